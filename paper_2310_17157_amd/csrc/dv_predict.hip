@@ -283,25 +283,43 @@ hipError_t launch_pred_scores(int wtype, const PredScoreArgs& a, hipStream_t st)
 }
 
 // ---------------------------------------------------------------- select
+// IPT: register slots per thread (wg_select_reg); 0: short vectors, ranked in LDS; -1:
+// streamed from memory. A kernel each: inlined side by side, the forms spill.
+template <int IPT, bool PAD>
 __global__ void __launch_bounds__(1024) k_select(const float* s, int n, int mode, int k, float thresh,
                                                  int32_t* idx, int cap, int32_t* count, int32_t* idx2) {
-  __shared__ uint32_t hist[kSelBins];
+  __shared__ uint32_t hist[IPT == 0 ? 1024 : kSelBins];
   __shared__ int sm[kSelSm(1024)];
   const int b = blockIdx.x;
-  if (n <= 1024)
-    wg_select_small<1024>(s + (size_t)b * n, n, mode, k, thresh, idx + (size_t)b * cap, cap,
-                          count ? count + b : nullptr, idx2 ? idx2 + (size_t)b * cap : nullptr, hist, sm);
-  else if (n <= 1024 * 48)
-    wg_select_reg<1024, 48>(s + (size_t)b * n, n, mode, k, thresh, idx + (size_t)b * cap, cap,
-                            count ? count + b : nullptr, idx2 ? idx2 + (size_t)b * cap : nullptr, hist, sm);
+  const float* sb = s + (size_t)b * n;
+  int32_t* ob = idx + (size_t)b * cap;
+  int32_t* cb = count ? count + b : nullptr;
+  int32_t* ob2 = idx2 ? idx2 + (size_t)b * cap : nullptr;
+  if constexpr (IPT == 0)
+    wg_select_small<1024>(sb, n, mode, k, thresh, ob, cap, cb, ob2, hist, sm);
+  else if constexpr (IPT > 0)
+    wg_select_reg<1024, IPT, true, PAD>(sb, n, mode, k, thresh, ob, cap, cb, ob2, hist, sm);
   else
-    wg_select<1024>(s + (size_t)b * n, n, mode, k, thresh, idx + (size_t)b * cap, cap,
-                    count ? count + b : nullptr, idx2 ? idx2 + (size_t)b * cap : nullptr, hist, sm);
+    wg_select<1024>(sb, n, mode, k, thresh, ob, cap, cb, ob2, hist, sm);
+}
+
+template <int IPT>
+static hipError_t launch_select_reg(dim3 grid, const float* scores, int n, int mode, int k, float thresh, int32_t* idx,
+                                    int cap, int32_t* count, int32_t* idx2, hipStream_t st) {
+  if constexpr (IPT > 4)
+    if (n <= 1024 * (IPT - 4))
+      return launch_select_reg<IPT - 4>(grid, scores, n, mode, k, thresh, idx, cap, count, idx2, st);
+  launch_k(n == 1024 * IPT ? k_select<IPT, false> : k_select<IPT, true>, grid, dim3(1024), 0, st, scores, n, mode, k,
+           thresh, idx, cap, count, idx2);
+  return hipGetLastError();
 }
 
 hipError_t launch_select(const float* scores, int B, int n, int mode, int k, float thresh,
                          int32_t* idx, int cap, int32_t* count, int32_t* idx2, hipStream_t st) {
-  launch_k(k_select, dim3(B), dim3(1024), 0, st, scores, n, mode, k, thresh, idx, cap, count, idx2);
+  if (n > 1024 && n <= 1024 * kSelIPT)
+    return launch_select_reg<kSelIPT>(dim3(B), scores, n, mode, k, thresh, idx, cap, count, idx2, st);
+  launch_k(n <= 1024 ? k_select<0, false> : k_select<-1, false>, dim3(B), dim3(1024), 0, st, scores, n, mode, k, thresh,
+           idx, cap, count, idx2);
   return hipGetLastError();
 }
 

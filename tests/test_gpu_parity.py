@@ -125,6 +125,37 @@ def test_select_paths_agree_with_oracle(n):
     assert host(idx)[0][:cap].tolist() == full[:cap]
 
 
+@pytest.mark.parametrize("n", [1026, 4095, 4096, 4097, 16383, 16384, 16388, 49152])
+def test_select_slots_per_thread(n):
+    """The register select keeps 4, 16 or 48 scores per thread by the vector's length (to
+    4096, 16384 and 49152 scores): at and beside those lengths, for two rows (the second
+    one misaligned when n is not a multiple of 4) of few distinct values, so that the
+    boundary ties, and a set of -inf, +inf, zeros of both signs and NaN-free extremes."""
+    d, r = 64, 8
+    AT = torch.zeros((r, d), dtype=torch.float32, device="cuda")
+    AT[0, 0] = 1.0
+    BT = torch.zeros((n, r), dtype=torch.float32, device="cuda")
+    vals = torch.tensor([float((i * 37) % 211) - 100.0 for i in range(n)])
+    vals[5], vals[n - 1], vals[n // 2], vals[0] = 3e38, -3e38, -0.0, 1e-45
+    BT[:, 0] = vals.cuda()
+    x = torch.zeros((2, d), dtype=torch.float32, device="cuda")
+    x[0, 0], x[1, 0] = 1.0, -1.0
+    pred = Bd.Predictor(AT, BT)
+    sc = torch.empty((2, n), dtype=torch.float32, device="cuda")
+    for k in (1, n // 20, n // 2, n - 1, n):
+        idx, cnt = Bd.dv_predict_mlp(pred, x, k, scores=sc)
+        _sync()
+        s = sc.cpu().double().numpy()
+        for b in range(2):
+            assert host(idx)[b].tolist() == O.select_topk(s[b], k).tolist(), (n, k, b)
+            assert int(cnt[b]) == k
+    idx, cnt = Bd.dv_predict_mlp(pred, x, mode=Bd.DV_SELECT_THRESHOLD, thresh=0.0)
+    _sync()
+    for b in range(2):
+        full = O.select_threshold(s[b], 0.0).tolist()
+        assert int(cnt[b]) == len(full) and host(idx)[b][: len(full)].tolist() == full
+
+
 def test_select_register_path_large_sets():
     """Register-resident selection (n <= 49152) of sets too large to stage in LDS
     (more than 8128 members) is written straight to memory: top-k with and without a

@@ -9,18 +9,20 @@
 //
 //   k_union_*     union of B ascending index sets (chunked bitmaps, then ranks), and
 //                 per-row membership bits of the sequences.
-//   k_ln_cast     x-hat = LN(x) (or x) as fp16 [NB][Kpad], zero padded.
-//   k_mfma_rows   P[s][r][b] = sum_{k in split s} W[row(r)][k] x-hat[b][k]: gathered
-//                 rows whose contraction index is contiguous in memory (fc1, Q/K/V,
-//                 predictor factors). A workgroup stages one K-split of x-hat in LDS;
-//                 each wavefront streams 16-row tiles straight into MFMA operands.
+//   k_ln_cast     x-hat = LN(x) (or x) as fp16 in k-steps, zero padded.
+//   k_rows        sum_k W[row(r)][k] x-hat[b][k]: gathered rows whose contraction index
+//                 is contiguous in memory (fc1, Q/K/V, predictor factors). A workgroup's
+//                 wavefronts split k, keep their part of x-hat in registers and apply
+//                 the epilogue (bias, sigma, masks, cache writes) to the summed tiles.
 //   k_mfma_cols   P2[s][b][n] = sum_{u in split s} C(b, u) M[row(u)][n]: gathered rows
 //                 contracted over the row index (fc2, out-projection). Row tiles are
 //                 written to a per-wavefront LDS tile (XOR-swizzled) and read back
 //                 column-wise with the LDS transpose read into the B operand.
-//   finishers     sum the split partials in a fixed order and apply bias, ReLU,
-//                 membership masks, cache writes and residuals.
+//   finishers     sum the split partials of k_mfma_cols in a fixed order with bias and
+//                 residual; combine split-KV partials.
 #include <math.h>
+
+#include <type_traits>
 
 #include "dv_internal.hpp"
 
@@ -91,9 +93,20 @@ __device__ __forceinline__ int byte_flags(uint32_t w) { return (int)((w * 0x0101
 template <bool MASK>
 __device__ __forceinline__ void union_chunk(const int32_t* __restrict__ sets, int B, int k, int n,
                                             int32_t* __restrict__ U, int32_t* __restrict__ count,
-                                            uint32_t* __restrict__ mask, int c, int nc, uint32_t* ush) {
+                                            uint32_t* __restrict__ mask, int32_t* __restrict__ slot, int c, int nc,
+                                            uint32_t* ush) {
   __shared__ int red[kUnionNT / 64 + 1];
   const int tid = threadIdx.x;
+  // slot[b][i] = i's place in set b or -1: each entry also clears the gap before it
+  if (slot != nullptr && c == nc - 1)
+    for (int e = tid; e < B * k; e += kUnionNT) {
+      const int b = e / k, j = e - b * k, v = min(max(sets[e], 0), n - 1);
+      int32_t* sl = slot + (size_t)b * n;
+      for (int i = j == 0 ? 0 : min(max(sets[e - 1], -1), n - 1) + 1; i < v; ++i) sl[i] = -1;
+      sl[v] = j;
+      if (j == k - 1)
+        for (int i = v + 1; i < n; ++i) sl[i] = -1;
+    }
   const int lo = c * kUnionChunk, hi = min(n, lo + kUnionChunk);
   const int n16 = (n + 15) & ~15;
   uint8_t* mk = reinterpret_cast<uint8_t*>(ush);
@@ -137,15 +150,15 @@ __device__ __forceinline__ void union_chunk(const int32_t* __restrict__ sets, in
 template <bool MASK>
 __global__ void __launch_bounds__(kUnionNT) k_union(const int32_t* __restrict__ sets, int B, int k, int n,
                                                     int32_t* __restrict__ U, int32_t* __restrict__ count,
-                                                    uint32_t* __restrict__ mask) {
+                                                    uint32_t* __restrict__ mask, int32_t* __restrict__ slot) {
   extern __shared__ __attribute__((aligned(16))) uint32_t ush[];
-  union_chunk<MASK>(sets, B, k, n, U, count, mask, blockIdx.x, gridDim.x, ush);
+  union_chunk<MASK>(sets, B, k, n, U, count, mask, slot, blockIdx.x, gridDim.x, ush);
 }
 
 size_t union_lds_bytes(int n) { return (size_t)((n + 15) & ~15) + (size_t)kUnionChunk * 4; }
 
 hipError_t launch_union(const int32_t* sets, int B, int k, int n, int32_t* U, int32_t* count, uint32_t* mask,
-                        hipStream_t st) {
+                        int32_t* slot, hipStream_t st) {
   const int nc = (n + kUnionChunk - 1) / kUnionChunk;
   const size_t lds = union_lds_bytes(n);
   const void* kern = mask != nullptr ? reinterpret_cast<const void*>(k_union<true>)
@@ -153,23 +166,23 @@ hipError_t launch_union(const int32_t* sets, int B, int k, int n, int32_t* U, in
   const hipError_t e = ensure_dyn_lds(kern, lds);
   if (e != hipSuccess) return e;
   if (mask != nullptr)
-    launch_k(k_union<true>, dim3(nc), dim3(kUnionNT), lds, st, sets, B, k, n, U, count, mask);
+    launch_k(k_union<true>, dim3(nc), dim3(kUnionNT), lds, st, sets, B, k, n, U, count, mask, slot);
   else
-    launch_k(k_union<false>, dim3(nc), dim3(kUnionNT), lds, st, sets, B, k, n, U, count, mask);
+    launch_k(k_union<false>, dim3(nc), dim3(kUnionNT), lds, st, sets, B, k, n, U, count, mask, slot);
   return hipGetLastError();
 }
 
 // --------------------------------------------------------------- x-hat cast
-// X16[b][0..Kpad) = fp16(LN(x[b])) (g == NULL: x[b]) for b < B; zero for b >= B
-// and for k >= d. One workgroup per row b of NB; d % 4 == 0, so rows move as float4.
+// X16(b, 0..Kpad) = fp16(LN(x[b])) (g == NULL: x[b]) for b < B; zero for b >= B
+// and for k >= d, in the layout of coef_index (a wavefront's B operand of one k-step is then
+// contiguous). One workgroup per row b of NB; d % 4 == 0, so rows move as float4.
 __device__ __forceinline__ void ln_cast_row(const float* __restrict__ x, int B, int d, int Kpad,
                                             const float* __restrict__ g, const float* __restrict__ be, float eps,
-                                            _Float16* __restrict__ X16, int b) {
+                                            _Float16* __restrict__ X16, int b, int NB) {
   __shared__ float red[16];
-  _Float16* o = X16 + (size_t)b * Kpad;
   const int n4 = d >> 2;
   if (b >= B) {
-    for (int k = threadIdx.x; k < Kpad; k += 1024) o[k] = (_Float16)0.f;
+    for (int k = threadIdx.x; k < Kpad; k += 1024) X16[coef_index(b, k, NB)] = (_Float16)0.f;
     return;
   }
   const f32x4* xr = reinterpret_cast<const f32x4*>(x + (size_t)b * d);
@@ -204,14 +217,14 @@ __device__ __forceinline__ void ln_cast_row(const float* __restrict__ x, int B, 
     f16x4 h;
 #pragma unroll
     for (int e = 0; e < 4; ++e) h[e] = (_Float16)v[e];
-    reinterpret_cast<f16x4*>(o)[i] = h;
+    *reinterpret_cast<f16x4*>(X16 + coef_index(b, 4 * i, NB)) = h;
   }
 }
 
 __global__ void __launch_bounds__(1024) k_ln_cast(const float* __restrict__ x, int B, int d, int Kpad,
                                                   const float* __restrict__ g, const float* __restrict__ be,
                                                   float eps, _Float16* __restrict__ X16) {
-  ln_cast_row(x, B, d, Kpad, g, be, eps, X16, blockIdx.x);
+  ln_cast_row(x, B, d, Kpad, g, be, eps, X16, blockIdx.x, gridDim.x);
 }
 
 // The cast and the union of the batch's sets in one launch (they are independent):
@@ -222,12 +235,12 @@ __global__ void __launch_bounds__(1024) k_cast_union(const float* __restrict__ x
                                                      float eps, _Float16* __restrict__ X16, int NB,
                                                      const int32_t* __restrict__ sets, int k, int n,
                                                      int32_t* __restrict__ U, int32_t* __restrict__ count,
-                                                     uint32_t* __restrict__ mask, int nc) {
+                                                     uint32_t* __restrict__ mask, int32_t* __restrict__ slot, int nc) {
   extern __shared__ __attribute__((aligned(16))) uint32_t ush[];
   if ((int)blockIdx.x < NB)
-    ln_cast_row(x, B, d, Kpad, g, be, eps, X16, blockIdx.x);
+    ln_cast_row(x, B, d, Kpad, g, be, eps, X16, blockIdx.x, NB);
   else
-    union_chunk<MASK>(sets, B, k, n, U, count, mask, (int)blockIdx.x - NB, nc, ush);
+    union_chunk<MASK>(sets, B, k, n, U, count, mask, slot, (int)blockIdx.x - NB, nc, ush);
 }
 
 hipError_t launch_ln_cast(const float* x, int B, int NB, int d, int Kpad, const float* g, const float* be, float eps,
@@ -238,7 +251,7 @@ hipError_t launch_ln_cast(const float* x, int B, int NB, int d, int Kpad, const 
 
 hipError_t launch_cast_union(const float* x, int B, int NB, int d, int Kpad, const float* g, const float* be,
                              float eps, _Float16* X16, const int32_t* sets, int k, int n, int32_t* U,
-                             int32_t* count, uint32_t* mask, hipStream_t st) {
+                             int32_t* count, uint32_t* mask, int32_t* slot, hipStream_t st) {
   static_assert(kUnionNT == 1024, "the cast and the union share the workgroup size");
   const int nc = (n + kUnionChunk - 1) / kUnionChunk;
   const size_t lds = union_lds_bytes(n);
@@ -248,252 +261,435 @@ hipError_t launch_cast_union(const float* x, int B, int NB, int d, int Kpad, con
   if (e != hipSuccess) return e;
   if (mask != nullptr)
     launch_k(k_cast_union<true>, dim3(NB + nc), dim3(1024), lds, st, x, B, d, Kpad, g, be, eps, X16, NB,
-                       sets, k, n, U, count, mask, nc);
+                       sets, k, n, U, count, mask, slot, nc);
   else
     launch_k(k_cast_union<false>, dim3(NB + nc), dim3(1024), lds, st, x, B, d, Kpad, g, be, eps, X16, NB,
-                       sets, k, n, U, count, mask, nc);
+                       sets, k, n, U, count, mask, slot, nc);
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------ k_mfma_rows
+// ----------------------------------------------------------------- k_rows
+// Gathered rows times the token batch, HBM-bound (a weight byte feeds 2 * NB / 2 flops). One
+// workgroup per CU takes a contiguous, even share of the rows (to one row, whatever the
+// count) over their whole length: its 8 wavefronts split the contraction index, so a
+// wavefront reads its part of the inputs once from L2 into registers (B operands) and uses
+// it for up to MT 16-row tiles, and the 8 partial sums are added through LDS, in wavefront
+// order, by the threads that apply the epilogue (bias, sigma, cache writes, casts). Nothing
+// is staged ahead of the stream, no split sum goes through memory and no finishing launch
+// follows. Against K splits over workgroups with the input slice in LDS, partials in
+// memory and a finishing launch (batch 32, OPT-175B shapes, us): QKV 146.5 + 11.7, fc1 of
+// 24950 rows 107.6 + 6.8; batch 8 at the OPT-6.7B shapes, where whole groups of workgroups had
+// no rows: predictor first layer 16.9 + 6.6, scores 22.4, QKV 24.9 + 4.9, fc1 19.2 + 4.5. This
+// form: QKV 158, fc1 104; first layer 8.3, scores 11.5, QKV 24.3, fc1 13.1.
+//
+// Per tile, each load instruction fetches whole 128-byte lines (8 rows x 8 lanes x 16
+// bytes): fetching the MFMA operand layout straight from memory (16 rows x 64 bytes per
+// instruction) runs at about 70% of the bandwidth of whole-line loads. Each 64-element
+// block of the tile's 16 rows is re-laid through a 2 KB per-wavefront LDS tile (16-byte
+// chunk c of row r stored at c ^ (r & 7), conflict-free both ways) into the A operand: lane
+// (lr, lg) takes row lr, chunk 4h + lg for k-step h of the block. A tile's reads go on for up to
+// four blocks (512 bytes of a row) before the next tile's.
+//
+// XF32: the inputs stay fp32 to 24 bits. A superblock (two blocks) of a token is scaled by a
+// power of two to below 2^14 and split into three fp16 terms (11 bits each), whose products
+// with the fp16 weights are exact; the fp32 sums over one superblock, of the first and of
+// the smaller terms apart, are added in fp64. Two terms would lose a bit and a half against
+// fp32, one fp32 sum over all superblocks another.
 template <int MODE>
-__device__ __forceinline__ int rows_count(const MrowsArgs& a) {
+__device__ __forceinline__ int rows_count(const RowsSrc& s) {
   if constexpr (MODE == kRowsIdentity) {
-    return a.nrows;
+    return s.nrows;
   } else {
-    const int c = a.list_count ? min(*a.list_count, a.list_max) : a.list_max;
-    return MODE == kRowsList ? c : 3 * c * a.dh;
+    const int c = s.list_count ? min(*s.list_count, s.list_max) : s.list_max;
+    return MODE == kRowsList ? c : 3 * c * s.dh;
   }
 }
 
-// Rows are addressed in two steps so that the index load of a tile can be issued well
-// ahead: rows_key(r) loads the list entry row r depends on (nothing for identity
-// rows), rows_addr(r, key) forms the address without further loads.
+// The weight row of contraction row r (the list lookup and the divisions, once per tile):
+// its index in W0 (list), or counted through W0, W1, W2 one after the other.
 template <int MODE>
-__device__ __forceinline__ int rows_key(const MrowsArgs& a, int r, int nrows) {
+__device__ __forceinline__ int rows_id(const RowsSrc& s, int r, int n) {
   if constexpr (MODE == kRowsIdentity) {
-    return 0;
+    return r;
   } else if constexpr (MODE == kRowsList) {
-    return a.list[r];
+    return min(max(s.list[r], 0), s.list_range - 1);
   } else {
-    const int per = nrows / 3;
-    return a.list[(r % per) / a.dh];
+    const int per = n / 3, m = r / per, rem = r - m * per, p = rem / s.dh;
+    return m * s.n0 + min(max(s.list[p], 0), s.list_range - 1) * s.dh + (rem - p * s.dh);
   }
 }
 template <int MODE>
-__device__ __forceinline__ const char* rows_addr(const MrowsArgs& a, int r, int key, int nrows) {
-  if constexpr (MODE == kRowsIdentity) {
-    return r < a.n0 ? static_cast<const char*>(a.W0) + (size_t)r * a.d * 2
-                    : static_cast<const char*>(a.W1) + (size_t)(r - a.n0) * a.d * 2;
+__device__ __forceinline__ const char* rows_addr(const RowsSrc& s, int id) {
+  const size_t rowb = (size_t)s.d * 2;
+  if constexpr (MODE == kRowsList) {
+    return static_cast<const char*>(s.W0) + (size_t)id * rowb;
+  } else if constexpr (MODE == kRowsIdentity) {
+    return id < s.n0 ? static_cast<const char*>(s.W0) + (size_t)id * rowb
+                     : static_cast<const char*>(s.W1) + (size_t)(id - s.n0) * rowb;
   } else {
-    const int k = min(max(key, 0), a.list_range - 1);
-    if constexpr (MODE == kRowsList) {
-      return static_cast<const char*>(a.W0) + (size_t)k * a.d * 2;
-    } else {
-      const int per = nrows / 3;
-      const int m = r / per;
-      const int t = (r - m * per) % a.dh;
-      const void* W = m == 0 ? a.W0 : (m == 1 ? a.W1 : a.W2);
-      return static_cast<const char*>(W) + ((size_t)k * a.dh + t) * a.d * 2;
-    }
+    const void* W = id < s.n0 ? s.W0 : (id < 2 * s.n0 ? s.W1 : s.W2);
+    const int o = id < s.n0 ? 0 : (id < 2 * s.n0 ? s.n0 : 2 * s.n0);
+    return static_cast<const char*>(W) + (size_t)(id - o) * rowb;
   }
 }
 
-constexpr int kMrTiles = 10;   // tiles a wavefront accumulates in registers at a time
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
-// One workgroup per CU. Per wavefront and 16-row tile, each load instruction fetches
-// whole 128-byte lines (8 rows x 8 lanes x 16 bytes): fetching the MFMA operand layout
-// straight from memory (16 rows x 64 bytes per instruction) runs at about 70% of the
-// bandwidth of whole-line loads. Each 64-element block of the tile's 16 rows is then
-// re-laid through a 2 KB per-wavefront LDS tile (16-byte chunk c of row r stored at
-// c ^ (r & 7), conflict-free both ways) into the A operand: lane (lr, lg) takes row lr,
-// chunk 4h + lg for k-step h of the block, which is exactly the k-range the B operand
-// (x-hat from LDS) supplies for that lane group.
-template <int NB, int NW, int U, int MODE>
-__global__ void __launch_bounds__(NW * 64) k_mfma_rows(MrowsArgs a) {
-  static_assert(U % 2 == 0, "a batch is whole 64-element blocks");
-  constexpr int NT = NW * 64;
-  constexpr int NBT = NB / 16;
-  extern __shared__ __attribute__((aligned(16))) _Float16 xs[];
-  const int tid = threadIdx.x;
-  const int s = blockIdx.x % a.S, g = blockIdx.x / a.S, G = gridDim.x / a.S;
-  const int ldx = a.Ks + 8;                     // halves per staged row (16-byte pad)
-  const int k0 = s * a.Ks;
-  // ---- stage x-hat[:, k0 : k0 + Ks) (zero beyond Kpad)
-  const int cpr = a.Ks >> 3;
-  for (int i = tid; i < NB * cpr; i += NT) {
-    const int b = i / cpr, c = i - b * cpr;
-    const int k = k0 + 8 * c;
-    const u32x4 v = k < a.Kpad ? ld_plain(a.X + (size_t)b * a.Kpad + k) : u32x4{0u, 0u, 0u, 0u};
-    *reinterpret_cast<u32x4*>(xs + b * ldx + 8 * c) = v;
+// Epilogue of one value: row r (of n), token b.
+template <int EPI, int NB, typename KT>
+__device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const RowsSrc& s, int r, int n, int b, int sp, float v) {
+  if constexpr (EPI == kEpiFc1) {
+    if (a.b1) v += a.b1[min(max(s.list[r], 0), s.list_range - 1)];
+    v = act_apply(v, a.act);
+    if (b >= a.B || (a.mask && !((a.mask[r] >> b) & 1u))) v = 0.f;
+    a.C[coef_index(b, r, NB)] = (_Float16)v;
+  } else if constexpr (EPI == kEpiQkv) {
+    const int g = r / s.dh, t = r - g * s.dh, nu = n / 3 / s.dh, m = g / nu;
+    const int h = min(max(s.list[g - m * nu], 0), s.list_range - 1);
+    if (b >= a.B) return;
+    const int jj = a.slot[b * s.list_range + h];   // h's place in the sequence's set, or -1
+    if (jj < 0 || jj >= a.n_heads) return;
+    const float* bias = m == 0 ? a.bq : (m == 1 ? a.bk : a.bv);
+    if (bias) v += bias[(size_t)h * s.dh + t];
+    if (m == 0) {
+      a.q[((size_t)b * a.n_heads + jj) * s.dh + t] = v;
+    } else {
+      KT* Cc = static_cast<KT*>(m == 1 ? a.K : a.V);
+      Cc[(((size_t)b * s.list_range + h) * a.cap + a.posb[b]) * s.dh + t] = (KT)v;
+    }
+  } else if constexpr (EPI == kEpiCoef) {   // the rows as the next contraction's fp16 inputs
+    if (r < s.n0)
+      a.C[coef_index(b, r, NB)] = (_Float16)v;
+    else
+      a.C1[coef_index(b, r - s.n0, NB)] = (_Float16)v;
+  } else {
+    if (b < a.B) s.out[(size_t)(sp * a.B + b) * s.nrows + r] = v;
   }
-  __syncthreads();
+}
 
-  const int n = rows_count<MODE>(a);
-  const int ntiles = (n + 15) >> 4;
-  const int wave = tid >> 6, lane = tid & 63;
+constexpr int kRowsNW = 8;
+// Tiles per round of the sums through LDS.
+template <int NB, bool XF32, int MT> constexpr int kRowsRT = MT < 5 ? MT : (XF32 && NB == 32 ? 2 : 5);
+template <int NB, bool XF32, int MT>
+constexpr size_t rows_lds() {
+  return (size_t)kRowsNW * (16 * 64 * 2 + kRowsRT<NB, XF32, MT> * 16 * (NB + 1) * (XF32 ? 8 : 4));
+}
+
+// MT: tiles a wavefront accumulates in registers at a time; SB: blocks of a superblock (a power
+// of two); TB: tiles whose loads are in flight together.
+template <int NB, int MODE, int EPI, bool XF32, typename KT, int MT, int SB, int TB>
+__global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
+  constexpr int NW = kRowsNW, NT = NW * 64, NBT = NB / 16;
+  constexpr int RT = kRowsRT<NB, XF32, MT>;
+  using Sum = std::conditional_t<XF32, double, float>;
+  extern __shared__ __attribute__((aligned(16))) _Float16 rsm[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  _Float16* at = xs + NB * ldx + wave * (16 * 64);    // this wavefront's re-layout tile
-  const int tstride = G * NW;
-  int tile = g * NW + wave;
-  if (tile >= ntiles) return;                    // no barrier follows
-  const int nbat = a.Ks / (32 * U);              // batches of U instructions (U/2 blocks)
-  const int kvalid = min(a.Ks, a.d - k0) * 2;    // valid bytes of this split in a row (>= 16)
+  _Float16* at = rsm + wave * (16 * 64);         // this wavefront's re-layout tile
+  Sum* red = reinterpret_cast<Sum*>(rsm + NW * 16 * 64);   // [NW][RT][16][NB + 1]
+  // workgroups [0, G0) take the first source's rows, the rest the second's
+  constexpr bool TWO = EPI == kEpiOut && !XF32;
+  const bool sec = TWO && (int)blockIdx.x >= a.G0;
+  const RowsSrc& s = TWO ? a.src[sec ? 1 : 0] : a.src[0];
+  const int S = XF32 ? a.S : 1, sp = XF32 ? (int)blockIdx.x % S : 0;   // split of the contraction
+  const int wg = TWO ? (int)blockIdx.x - (sec ? a.G0 : 0) : (int)blockIdx.x / S;
+  const int G = TWO ? (sec ? (int)gridDim.x - a.G0 : a.G0) : (int)gridDim.x / S;
+  if constexpr (EPI == kEpiQkv) {
+    // the attention's coefficient matrix, before it writes its part
+    if (a.zero != nullptr)
+      for (int i = (int)blockIdx.x * NT + tid; i < a.zero_n / 8; i += (int)gridDim.x * NT)
+        reinterpret_cast<u32x4*>(a.zero)[i] = u32x4{0u, 0u, 0u, 0u};
+  }
+  const int n = rows_count<MODE>(s);
+  const int r0 = (int)((long)wg * n / G), r1 = (int)((long)(wg + 1) * n / G);
+  const int nblk = (s.d + 63) >> 6;              // 64-element blocks of a row
+  // (a contiguous part each: with superblocks dealt to the wavefronts in turn, QKV at batch
+  // 32 took 172 us instead of 158)
+  const int sb0 = sp * nblk / S, sbn = (sp + 1) * nblk / S - sb0;
+  const int kb0 = sb0 + wave * sbn / NW, kb1 = sb0 + (wave + 1) * sbn / NW;
+  const int dbytes = s.d * 2;
   const int cb = (lane & 7) * 16;                // this lane's 16 bytes of a 128-byte block
-  const int rl0 = lane >> 3, rl1 = 8 + (lane >> 3);   // its rows of a tile (even / odd loads)
+  const int rl0 = lane >> 3;                     // its rows of a tile: rl0 and rl0 + 8
 
-  auto key_of = [&](int t, int rl) { return rows_key<MODE>(a, min(t * 16 + rl, n - 1), n); };
-  // One batch: U loads of tile t's rows (chunks past the row or past n are clamped,
-  // in-bounds loads, zeroed only when written to LDS, so that no select waits on a
-  // load right after issuing it), then its U/2 blocks re-laid and multiplied.
-  auto batch = [&](int t, int key0, int key1, int bi, f32x4 (&acc)[NBT]) {
-    const int r0 = t * 16 + rl0, r1 = t * 16 + rl1;
-    const char* p0 = rows_addr<MODE>(a, min(r0, n - 1), key0, n) + k0 * 2;
-    const char* p1 = rows_addr<MODE>(a, min(r1, n - 1), key1, n) + k0 * 2;
-    u32x4 w[U];
-    unsigned okm = 0u;
+  for (int c0 = r0; c0 < r1; c0 += 16 * MT) {
+    const int T = min(MT, (r1 - c0 + 15) >> 4);
+    int id0[MT], id1[MT];                        // (past the share: its last row again)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int off = (bi * (U / 2) + (u >> 1)) * 128 + cb;
-      okm |= (off < kvalid && ((u & 1) ? r1 : r0) < n) ? (1u << u) : 0u;
-      w[u] = ld_stream(((u & 1) ? p1 : p0) + min(off, kvalid - 16));
+    for (int q = 0; q < MT; ++q) {
+      id0[q] = rows_id<MODE>(s, min(c0 + 16 * q + rl0, r1 - 1), n);
+      id1[q] = rows_id<MODE>(s, min(c0 + 16 * q + rl0 + 8, r1 - 1), n);
     }
+    Sum acc[MT][NBT][4];
 #pragma unroll
-    for (int blk = 0; blk < U / 2; ++blk) {
+    for (int q = 0; q < MT; ++q)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r = rl0 + 8 * i, c = lane & 7;
-        const int u = 2 * blk + i;
-        *reinterpret_cast<u32x4*>(at + r * 64 + ((c ^ (r & 7)) << 3)) =
-            ((okm >> u) & 1u) ? w[u] : u32x4{0u, 0u, 0u, 0u};
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      for (int j = 0; j < NBT; ++j)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int c = 4 * h + lg;
-        const f16x8 av = *reinterpret_cast<const f16x8*>(at + lr * 64 + ((c ^ (lr & 7)) << 3));
-        const int ks = 2 * (bi * (U / 2) + blk) + h;
+        for (int i = 0; i < 4; ++i) acc[q][j][i] = 0;
+
+    auto super = [&](auto blocks, int kb) {
+      constexpr int NBLK = decltype(blocks)::value;
+      constexpr int TERMS = XF32 ? 3 : 1;
+      f16x8 bf[2 * NBLK][NBT][TERMS];
+      float inv[NBT];
+      auto load_w = [&](u32x4 (&w)[2 * NBLK], int q) {
+        // (opaque, so that the addresses of all tiles are not kept in registers across superblocks)
+        int i0 = id0[q], i1 = id1[q];
+        asm volatile("" : "+v"(i0), "+v"(i1));
+        const char* p0 = rows_addr<MODE>(s, i0);
+        const char* p1 = rows_addr<MODE>(s, i1);
 #pragma unroll
-        for (int j = 0; j < NBT; ++j) {
-          const f16x8 bv = *reinterpret_cast<const f16x8*>(xs + (lr + 16 * j) * ldx + 32 * ks + 8 * lg);
-          acc[j] = mfma16x16x32(av, bv, acc[j]);
+        for (int u = 0; u < 2 * NBLK; ++u) {
+          const int off = (kb + (u >> 1)) * 128 + cb;          // (past the row: its last 16 bytes, then zeroed)
+          w[u] = ld_stream(((u & 1) ? p1 : p0) + min(off, dbytes - 16));
         }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-  };
-  // This wavefront's tiles are tile, tile + tstride, ...; up to kMrTiles of them at a time
-  // keep their accumulators in registers, and their results are written once all of
-  // them are done. Written per tile instead, the partials (a few hundred bytes per
-  // wavefront, every few microseconds) interleave DRAM writes with the weight stream,
-  // which cost far more than their bytes: at batch 32, QKV 175 us against 142 us with
-  // the stores kept in L2. Each tile's rows are read to the end of the split before the
-  // next tile starts (QKV at batch 32: 154 us, against 161-167 us with the batch loop
-  // outside, which jumps between tiles every 512 bytes of a row).
-  const int mine = (ntiles - tile + tstride - 1) / tstride;
-  for (int c0 = 0; c0 < mine; c0 += kMrTiles) {
-    int key0[kMrTiles], key1[kMrTiles];
+      };
+      // XF32: the first tiles' weights are on their way while the inputs are split
+      u32x4 wf[XF32 ? TB : 1][2 * NBLK];
+      if constexpr (XF32) {
+        f32x4 xv[2 * NBLK][NBT][2];
 #pragma unroll
-    for (int q = 0; q < kMrTiles; ++q) {
-      const int t = tile + min(c0 + q, mine - 1) * tstride;   // (clamped, unconditional)
-      key0[q] = key_of(t, rl0);
-      key1[q] = key_of(t, rl1);
-    }
-    f32x4 acc[kMrTiles][NBT];
+        for (int ks = 0; ks < 2 * NBLK; ++ks) {
+          const int k = (2 * kb + ks) * 32 + 8 * lg;
 #pragma unroll
-    for (int q = 0; q < kMrTiles; ++q)
-#pragma unroll
-      for (int j = 0; j < NBT; ++j) acc[q][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < kMrTiles; ++q)
-      if (c0 + q < mine)
-        for (int bi = 0; bi < nbat; ++bi) batch(tile + (c0 + q) * tstride, key0[q], key1[q], bi, acc[q]);
-#pragma unroll
-    for (int q = 0; q < kMrTiles; ++q) {
-      if (c0 + q >= mine) continue;
-      const int t = tile + (c0 + q) * tstride;
-      // lane holds rows t*16 + 4*lg + i, token columns lr + 16*j
-      if (a.out0 != nullptr) {
-#pragma unroll
-        for (int j = 0; j < NBT; ++j) {
-          const int b = lr + 16 * j;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int r = t * 16 + 4 * lg + i;
-            if (r < n && b < a.B) {
-              if (r < a.n0) a.out0[(size_t)b * a.ld0 + r] = acc[q][j][i];
-              else a.out1[(size_t)b * a.ld1 + (r - a.n0)] = acc[q][j][i];
+          for (int j = 0; j < NBT; ++j) {
+            const float* xp = static_cast<const float*>(s.X) + (size_t)min(lr + 16 * j, a.B - 1) * s.d + min(k, s.d - 8);
+            xv[ks][j][0] = *reinterpret_cast<const f32x4*>(xp);
+            xv[ks][j][1] = *reinterpret_cast<const f32x4*>(xp + 4);
+            for (int p = 1; p < a.XP; ++p) {     // inputs given as parts (few): their sum
+              const float* pp = xp + (size_t)p * a.B * s.d;
+              xv[ks][j][0] += *reinterpret_cast<const f32x4*>(pp);
+              xv[ks][j][1] += *reinterpret_cast<const f32x4*>(pp + 4);
             }
           }
         }
+#pragma unroll
+        for (int tt = 0; tt < TB; ++tt) load_w(wf[tt], tt);
+#pragma unroll
+        for (int j = 0; j < NBT; ++j) {
+          float m = 0.f;
+#pragma unroll
+          for (int ks = 0; ks < 2 * NBLK; ++ks) {
+            const bool in = (2 * kb + ks) * 32 + 8 * lg < s.d;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float v = in ? xv[ks][j][e >> 2][e & 3] : 0.f;
+              xv[ks][j][e >> 2][e & 3] = v;
+              m = fmaxf(m, fabsf(v));
+            }
+          }
+          m = fmaxf(m, __shfl_xor(m, 16, kWave));
+          m = fmaxf(m, __shfl_xor(m, 32, kWave));
+          // 2^(13 - floor(log2 m)), at most 2^126 (zeros and subnormals), from the exponent bits
+          const int e2 = min(max(140 - (int)((__float_as_uint(m) >> 23) & 255u), -126), 126);
+          const float sc = __uint_as_float((uint32_t)(e2 + 127) << 23);
+          inv[j] = __uint_as_float((uint32_t)(127 - e2) << 23);
+#pragma unroll
+          for (int ks = 0; ks < 2 * NBLK; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float v = xv[ks][j][e >> 2][e & 3] * sc;
+              const _Float16 hi = (_Float16)v;
+              float rest = v - (float)hi;
+              rest = fabsf(v) < 32768.f ? rest : 0.f;          // (infinities and NaN: the first term alone)
+              const _Float16 mid = (_Float16)rest;
+              bf[ks][j][0][e] = (_Float16)(rest - (float)mid);
+              bf[ks][j][TERMS - 2][e] = mid;
+              bf[ks][j][TERMS - 1][e] = hi;
+            }
+        }
       } else {
-        // whole rows of NB floats with 16-byte stores, through the wavefront's LDS tile
-        float* tf = reinterpret_cast<float*>(at);        // [16][NB] fp32 (<= the 2 KB tile)
+#pragma unroll
+        for (int ks = 0; ks < 2 * NBLK; ++ks)
+#pragma unroll
+          for (int j = 0; j < NBT; ++j)
+            bf[ks][j][0] = __builtin_bit_cast(
+                f16x8, ld_plain(static_cast<const _Float16*>(s.X) + coef_index(lr + 16 * j, (2 * kb + ks) * 32 + 8 * lg, NB)));
+      }
+      // N tiles from q0: their loads all in flight, then each re-laid and multiplied
+      auto tiles = [&](auto count, int q0) {
+        constexpr int N = decltype(count)::value;
+        u32x4 w[N][2 * NBLK];
+#pragma unroll
+        for (int tt = 0; tt < N; ++tt) {
+          if (XF32 && q0 + tt < TB) {
+#pragma unroll
+            for (int u = 0; u < 2 * NBLK; ++u) w[tt][u] = wf[XF32 ? q0 + tt : 0][u];
+          } else {
+            load_w(w[tt], q0 + tt);
+          }
+        }
+#pragma unroll
+        for (int tt = 0; tt < N; ++tt) {
+          const int q = q0 + tt;
+          f32x4 t[NBT], tl[NBT];                               // (XF32: the first terms; the small ones)
+#pragma unroll
+          for (int j = 0; j < NBT; ++j) {
+            tl[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (XF32) t[j] = tl[j];
+            else t[j] = f32x4{acc[q][j][0], acc[q][j][1], acc[q][j][2], acc[q][j][3]};
+          }
+#pragma unroll
+          for (int blk = 0; blk < NBLK; ++blk) {
+            const bool in = (kb + blk) * 128 + cb < dbytes;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              const int r = rl0 + 8 * i, c = lane & 7;
+              *reinterpret_cast<u32x4*>(at + r * 64 + ((c ^ (r & 7)) << 3)) =
+                  in ? w[tt][2 * blk + i] : u32x4{0u, 0u, 0u, 0u};
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const f16x8 av = *reinterpret_cast<const f16x8*>(at + lr * 64 + (((4 * h + lg) ^ (lr & 7)) << 3));
+#pragma unroll
+              for (int j = 0; j < NBT; ++j) {
+                if constexpr (XF32) {
+                  tl[j] = mfma16x16x32(av, bf[2 * blk + h][j][0], tl[j]);
+                  tl[j] = mfma16x16x32(av, bf[2 * blk + h][j][1], tl[j]);
+                }
+                t[j] = mfma16x16x32(av, bf[2 * blk + h][j][TERMS - 1], t[j]);
+              }
+            }
+            wave_lds_fence();
+          }
+#pragma unroll
+          for (int j = 0; j < NBT; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              if constexpr (XF32) acc[q][j][i] += ((double)t[j][i] + (double)tl[j][i]) * (double)inv[j];
+              else acc[q][j][i] = t[j][i];
+            }
+        }
+      };
+#pragma unroll
+      for (int q0 = 0; q0 < MT; q0 += TB) {
+        if (q0 + TB <= T && q0 + TB <= MT) {
+          tiles(std::integral_constant<int, TB>{}, q0);
+        } else {
+#pragma unroll
+          for (int q = q0; q < q0 + TB && q < MT; ++q)
+            if (q < T) tiles(std::integral_constant<int, 1>{}, q);
+        }
+      }
+    };
+    int kb = kb0;
+    for (; kb + SB <= kb1; kb += SB) super(std::integral_constant<int, SB>{}, kb);
+    if constexpr (SB > 4)
+      if (kb + 4 <= kb1) {
+        super(std::integral_constant<int, 4>{}, kb);
+        kb += 4;
+      }
+    if constexpr (SB > 2)
+      if (kb + 2 <= kb1) {
+        super(std::integral_constant<int, 2>{}, kb);
+        kb += 2;
+      }
+    for (; kb < kb1; ++kb) super(std::integral_constant<int, 1>{}, kb);
+
+    // ---- the wavefronts' sums added in order, RT tiles at a time (lane: rows 4 lg + i,
+    // tokens lr + 16 j of a tile)
+#pragma unroll
+    for (int t0 = 0; t0 < MT; t0 += RT) {
+      if (t0 >= T) continue;
+      __syncthreads();
+#pragma unroll
+      for (int q = t0; q < t0 + RT && q < MT; ++q)
 #pragma unroll
         for (int j = 0; j < NBT; ++j)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) tf[(4 * lg + i) * NB + lr + 16 * j] = acc[q][j][i];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        constexpr int LPRW = NB / 4, RPI = 64 / LPRW;   // lanes per row, rows per instruction
-        const int cq = 4 * (lane % LPRW);
+          for (int i = 0; i < 4; ++i)
+            red[((wave * RT + (q - t0)) * 16 + 4 * lg + i) * (NB + 1) + lr + 16 * j] = acc[q][j][i];
+      __syncthreads();
+      for (int e = tid; e < min(RT, T - t0) * 16 * NB; e += NT) {
+        const int rr = e & 15, b = (e >> 4) % NB, q = (e >> 4) / NB;
+        const int r = c0 + 16 * (t0 + q) + rr;
+        if (r >= r1) continue;
+        Sum v = 0;
 #pragma unroll
-        for (int rr = lane / LPRW; rr < 16; rr += RPI) {
-          const int r = t * 16 + rr;
-          if (r < n)
-            *reinterpret_cast<f32x4*>(a.P + ((size_t)s * a.nrows_pad + r) * NB + cq) =
-                *reinterpret_cast<const f32x4*>(tf + rr * NB + cq);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int w = 0; w < NW; ++w) v += red[((w * RT + q) * 16 + rr) * (NB + 1) + b];
+        rows_epilogue<EPI, NB, KT>(a, s, r, n, b, sp, (float)v);
       }
+    }
+  }
+  // zero rows up to the next contraction's whole k-steps (by the last workgroup)
+  if constexpr (EPI == kEpiFc1) {
+    if (wg == G - 1) {
+      const int pad = ((n + 31) & ~31) - n;
+      for (int e = tid; e < pad * NB; e += NT) a.C[coef_index(e / pad, n + e % pad, NB)] = (_Float16)0.f;
+    }
+  }
+  if constexpr (EPI == kEpiCoef) {
+    if (wg == G - 1) {
+      const int n1 = n - s.n0, p0 = ((s.n0 + 63) & ~63) - s.n0, p1 = ((n1 + 63) & ~63) - n1;
+      for (int e = tid; e < p0 * NB; e += NT) a.C[coef_index(e / p0, s.n0 + e % p0, NB)] = (_Float16)0.f;
+      if (a.C1 != nullptr)
+        for (int e = tid; e < p1 * NB; e += NT) a.C1[coef_index(e / p1, n1 + e % p1, NB)] = (_Float16)0.f;
     }
   }
 }
 
-// K per split for k_mfma_rows: a multiple of 32 * kMrU halves whose staged slice of
-// NB rows fits 96 KB of LDS (with the re-layout tiles, one workgroup per CU).
-static constexpr int kMrU = 8, kMrNW = 8;
-static constexpr int kMrTileBytes = kMrNW * 16 * 64 * 2;
-void mrows_split(int Kpad, int NB, int* S, int* Ks) {
-  const int budget = min(device_lds_per_block() - kMrTileBytes, 98304 + NB * 16);
-  const int unit = 32 * kMrU;
-  int kmax = ((budget / (NB * 2) - 8) / unit) * unit;
-  if (kmax < unit) kmax = unit;
-  int s = (Kpad + kmax - 1) / kmax;
-  int ks = (((Kpad + s - 1) / s) + unit - 1) / unit * unit;
-  *S = s;
-  *Ks = ks;
-}
-
-template <int NB, int MODE>
-static hipError_t launch_mrows_t(MrowsArgs a, hipStream_t st) {
-  const size_t lds = (size_t)NB * (a.Ks + 8) * 2 + kMrTileBytes;
-  const auto kern = k_mfma_rows<NB, kMrNW, kMrU, MODE>;
+template <int NB, int MODE, int EPI, bool XF32, typename KT, int MT, int SB, int TB>
+static hipError_t launch_rows_v(const RowsArgs& a, int G, hipStream_t st) {
+  constexpr size_t lds = rows_lds<NB, XF32, MT>();
+  const auto kern = k_rows<NB, MODE, EPI, XF32, KT, MT, SB, TB>;
   const hipError_t e = ensure_dyn_lds(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
-  const int G = max(1, device_cu_count() / a.S);
-  launch_k(kern, dim3(G * a.S), dim3(kMrNW * 64), lds, st, a);
+  launch_k(kern, dim3(G), dim3(kRowsNW * 64), lds, st, a);
   return hipGetLastError();
 }
 
-template <int NB>
-static hipError_t launch_mrows_nb(const MrowsArgs& a, hipStream_t st) {
-  switch (a.mode) {
-    case kRowsList: return launch_mrows_t<NB, kRowsList>(a, st);
-    case kRowsHeads: return launch_mrows_t<NB, kRowsHeads>(a, st);
-    default: return launch_mrows_t<NB, kRowsIdentity>(a, st);
+// Splits of the contraction of a fp32-input launch with few rows: 16-row tiles times splits
+// fill the CUs once (every workgroup splits its part of the inputs itself, so workgroups of
+// a few rows over the whole length would mostly repeat that: predictor of rank 1000, width
+// 9216, 16 inputs, 26.8 us).
+int rows_splits(int nrows) { return min(max(device_cu_count() / ((nrows + 15) / 16), 1), kRowsMaxSplit); }
+
+template <int NB, int MODE, int EPI, bool XF32, typename KT>
+static hipError_t launch_rows_t(RowsArgs a, hipStream_t st) {
+  // one workgroup per CU; two sources share them by their rows' bytes
+  const int G = max(device_cu_count(), 2);
+  const double w0 = (double)a.src[0].nrows * a.src[0].d, w1 = (double)a.src[1].nrows * a.src[1].d;
+  a.G0 = a.src[1].W0 == nullptr ? G : min(max((int)(G * w0 / (w0 + w1) + 0.5), 1), G - 1);
+  if constexpr (XF32) {
+    // (tiles in flight at the OPT-66B predictor's scores, 16 inputs: 1, 2, 3, 5: 24.1, 21.4, 21.7,
+    // 31.5 us)
+    if (a.S > 1)
+      return launch_rows_v<NB, MODE, EPI, XF32, KT, 1, NB == 16 ? 4 : 2, 1>(a, (a.src[0].nrows + 15) / 16 * a.S, st);
+    a.S = 1;
+    return launch_rows_v<NB, MODE, EPI, XF32, KT, NB == 16 ? 10 : 4, 2, NB == 16 ? 2 : 1>(a, G, st);
+  } else {
+    // few rows (to one tile per workgroup): one tile, longer superblocks. Otherwise two tiles'
+    // loads in flight with 16 tokens (four: QKV of the OPT-6.7B heads 29.5 against 24.4 us), one
+    // with 32 (two spill)
+    if constexpr (MODE == kRowsIdentity)
+      if (a.src[1].W0 == nullptr && a.src[0].nrows <= 16 * G)
+        return launch_rows_v<NB, MODE, EPI, XF32, KT, 1, NB == 16 ? 8 : 4, 1>(a, G, st);
+    return launch_rows_v<NB, MODE, EPI, XF32, KT, 10, 4, NB == 16 ? 2 : 1>(a, G, st);
   }
 }
 
-hipError_t launch_mrows(int NB, const MrowsArgs& a, hipStream_t st) {
-  return NB <= 16 ? launch_mrows_nb<16>(a, st) : launch_mrows_nb<32>(a, st);
+template <int NB>
+static hipError_t launch_rows_nb(int epi, int kvtype, bool xf32, const RowsArgs& a, hipStream_t st) {
+  switch (epi) {
+    case kEpiFc1: return launch_rows_t<NB, kRowsList, kEpiFc1, false, float>(a, st);
+    case kEpiQkv:
+      return kvtype == DV_F16 ? launch_rows_t<NB, kRowsHeads, kEpiQkv, false, _Float16>(a, st)
+                              : launch_rows_t<NB, kRowsHeads, kEpiQkv, false, float>(a, st);
+    case kEpiCoef: return launch_rows_t<NB, kRowsIdentity, kEpiCoef, false, float>(a, st);
+    default:
+      return xf32 ? launch_rows_t<NB, kRowsIdentity, kEpiOut, true, float>(a, st)
+                  : launch_rows_t<NB, kRowsIdentity, kEpiOut, false, float>(a, st);
+  }
+}
+
+hipError_t launch_rows(int NB, int epi, int kvtype, bool xf32, const RowsArgs& a, hipStream_t st) {
+  return NB <= 16 ? launch_rows_nb<16>(epi, kvtype, xf32, a, st) : launch_rows_nb<32>(epi, kvtype, xf32, a, st);
 }
 
 // ------------------------------------------------------------ k_mfma_cols
@@ -717,9 +913,7 @@ hipError_t launch_mcols(int NB, const McolsArgs& a, hipStream_t st) {
 }
 
 // --------------------------------------------------------------- finishers
-// sum_{s < S} P[s * stride + e] in split order, with up to 8 loads in flight.
-// Four consecutive elements summed over the splits in split order (the same order, so
-// the same bits, as sum_splits per element); every split's load is issued before the
+// Four consecutive elements summed over the splits in split order; every split's load is issued before the
 // first add, unpredicated (split index clamped, surplus not added).
 __device__ __forceinline__ f32x4 sum_splits4(const float* __restrict__ P, int S, size_t stride, size_t e) {
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -732,63 +926,6 @@ __device__ __forceinline__ f32x4 sum_splits4(const float* __restrict__ P, int S,
       if (s0 + u < S) v += t[u];
   }
   return v;
-}
-
-__device__ __forceinline__ float sum_splits(const float* __restrict__ P, int S, size_t stride, size_t e) {
-  float v = 0.f;
-  for (int s0 = 0; s0 < S; s0 += 8) {
-    float t[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = s0 + u < S ? P[(size_t)(s0 + u) * stride + e] : 0.f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v += t[u];
-  }
-  return v;
-}
-
-// fc1: C(b, u) = fp16(ReLU(sum_s P[s][u][b] + b1[list[u]])) for b < B and u < n (and,
-// with a mask, only where bit b of mask[u] is set); zero elsewhere up to a multiple
-// of 64 rows. One workgroup per 64 rows.
-template <int NB>
-__global__ void __launch_bounds__(16 * NB) k_fc1_finish(Fc1FinishArgs a) {
-  // one thread per four tokens of one of the workgroup's 64 rows: a single round trip
-  __shared__ float t[64][NB + 1];
-  const int n = a.list_count ? min(*a.list_count, a.list_max) : a.list_max;
-  const int u0 = blockIdx.x * 64;
-  if (u0 >= ((n + 63) & ~63)) return;
-  {
-    const int ul = threadIdx.x / (NB / 4), b0 = (threadIdx.x - ul * (NB / 4)) * 4;
-    const int u = u0 + ul;
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (u < n) {
-      v = sum_splits4(a.P, a.S, (size_t)a.nrows_pad * NB, (size_t)u * NB + b0);
-      const float bias = a.b1 ? a.b1[min(max(a.list[u], 0), a.list_range - 1)] : 0.f;
-      const uint32_t mk = a.mask ? a.mask[u] : 0xffffffffu;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float x = v[i] + bias;
-        x = act_apply(x, a.act);
-        if (b0 + i >= a.B || !((mk >> (b0 + i)) & 1u)) x = 0.f;
-        v[i] = x;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) t[ul][b0 + i] = v[i];
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 64 * NB; e += 16 * NB) {
-    const int b = e >> 6, ul = e & 63;
-    a.C[coef_index(b, u0 + ul, NB)] = (_Float16)t[ul][b];
-  }
-}
-
-hipError_t launch_fc1_finish(int NB, const Fc1FinishArgs& a, hipStream_t st) {
-  const int blocks = max(1, (a.list_max + 63) / 64);
-  if (NB <= 16)
-    launch_k(k_fc1_finish<16>, dim3(blocks), dim3(16 * 16), 0, st, a);
-  else
-    launch_k(k_fc1_finish<32>, dim3(blocks), dim3(16 * 32), 0, st, a);
-  return hipGetLastError();
 }
 
 // Sum of k_mfma_cols partials: out[b][c] = sum_s P2[s][b][c] + bias[c] + resid[b][c];
@@ -807,100 +944,6 @@ __global__ void __launch_bounds__(256) k_cols_finish(ColsFinishArgs a) {
 hipError_t launch_cols_finish(const ColsFinishArgs& a, hipStream_t st) {
   const long quads = ((long)a.B * a.d / 4 + 255) / 256;
   launch_k(k_cols_finish, dim3((unsigned)max(1L, quads)), dim3(256), 0, st, a);
-  return hipGetLastError();
-}
-
-// Predictor hidden layer: C[b][j] = fp16(sum_s P[s][j][b]) for j < r, b < B (zero
-// padding to ldc columns and NB rows).
-template <int NB>
-__global__ void __launch_bounds__(256) k_sum_cast(const float* __restrict__ P, int S, int nrows_pad, int row0,
-                                                  int r, int B, _Float16* __restrict__ C, int ldc) {
-  const int total = NB * ldc;
-  for (int e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
-    const int b = e / ldc, j = e - b * ldc;
-    float v = 0.f;
-    if (b < B && j < r) v = sum_splits(P, S, (size_t)nrows_pad * NB, (size_t)(row0 + j) * NB + b);
-    C[e] = (_Float16)v;
-  }
-}
-
-hipError_t launch_sum_cast(int NB, const float* P, int S, int nrows_pad, int row0, int r, int B, _Float16* C, int ldc,
-                           hipStream_t st) {
-  const int blocks = min((NB * ldc + 255) / 256, 4 * device_cu_count());
-  if (NB <= 16)
-    launch_k(k_sum_cast<16>, dim3(blocks), dim3(256), 0, st, P, S, nrows_pad, row0, r, B, C, ldc);
-  else
-    launch_k(k_sum_cast<32>, dim3(blocks), dim3(256), 0, st, P, S, nrows_pad, row0, r, B, C, ldc);
-  return hipGetLastError();
-}
-
-// Q/K/V of the batch. One workgroup per (union head p, projection m): the dh x NB
-// partial sums of its rows are read contiguously, summed over the splits in order and
-// biased; then for every sequence b whose set holds h = list[p] (as its j-th head) the
-// query goes to q[b][j][:] (m = 0) or the key/value to cache row pos[b] of head h
-// (m = 1, 2; round to nearest even).
-template <int NB, typename KT>
-__global__ void __launch_bounds__(1024) k_qkv_finish(QkvFinishArgs a) {
-  extern __shared__ float qsm[];                  // [dh][NB + 1]
-  __shared__ int jsel[NB];
-  const int p = blockIdx.x, m = blockIdx.y;
-  if (a.zero != nullptr) {   // the attention's coefficient matrix, before it writes its part
-    const int wg = blockIdx.x + gridDim.x * blockIdx.y, nwg = gridDim.x * gridDim.y;
-    for (int i = wg * 1024 + (int)threadIdx.x; i < a.zero_n / 8; i += nwg * 1024)
-      reinterpret_cast<u32x4*>(a.zero)[i] = u32x4{0u, 0u, 0u, 0u};
-  }
-  const int nu = *a.hcount;
-  if (p >= nu) return;
-  const int h = min(max(a.hlist[p], 0), a.H - 1);
-  if (threadIdx.x < NB) {
-    int jj = -1;
-    const int b = threadIdx.x;
-    if (b < a.B) {
-      const int32_t* hs = a.heads + (size_t)b * a.n_heads;
-      int lo = 0, hi = a.n_heads - 1;
-      while (lo <= hi) {
-        const int mid = (lo + hi) >> 1;
-        if (hs[mid] == h) { jj = mid; break; }
-        if (hs[mid] < h) lo = mid + 1; else hi = mid - 1;
-      }
-    }
-    jsel[b] = jj;
-  }
-  const size_t r0 = ((size_t)m * nu + p) * a.dh;
-  const float* bias = m == 0 ? a.bq : (m == 1 ? a.bk : a.bv);
-  // one thread per four tokens of a row: every split's load in flight at once
-  for (int e = threadIdx.x * 4; e < a.dh * NB; e += 1024 * 4) {
-    const int t = e / NB, b = e - t * NB;
-    f32x4 v = sum_splits4(a.P, a.S, (size_t)a.nrows_pad * NB, (r0 + t) * NB + b);
-    const float bs = bias ? bias[(size_t)h * a.dh + t] : 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) qsm[t * (NB + 1) + b + i] = v[i] + bs;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < a.dh * NB; e += 1024) {
-    const int b = e / a.dh, t = e - b * a.dh;
-    const int jj = jsel[b];
-    if (jj < 0) continue;
-    const float v = qsm[t * (NB + 1) + b];
-    if (m == 0) {
-      a.q[((size_t)b * a.n_heads + jj) * a.dh + t] = v;
-    } else {
-      KT* Cc = static_cast<KT*>(m == 1 ? a.K : a.V);
-      Cc[(((size_t)b * a.H + h) * a.cap + a.posb[b]) * a.dh + t] = (KT)v;
-    }
-  }
-}
-
-hipError_t launch_qkv_finish(int NB, int kvtype, const QkvFinishArgs& a, hipStream_t st) {
-  dim3 grid(a.H, 3);
-  const size_t lds = (size_t)a.dh * (NB + 1) * sizeof(float);
-  if (NB <= 16) {
-    if (kvtype == DV_F16) launch_k((k_qkv_finish<16, _Float16>), grid, dim3(1024), lds, st, a);
-    else launch_k((k_qkv_finish<16, float>), grid, dim3(1024), lds, st, a);
-  } else {
-    if (kvtype == DV_F16) launch_k((k_qkv_finish<32, _Float16>), grid, dim3(1024), lds, st, a);
-    else launch_k((k_qkv_finish<32, float>), grid, dim3(1024), lds, st, a);
-  }
   return hipGetLastError();
 }
 

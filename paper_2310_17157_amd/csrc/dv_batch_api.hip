@@ -3,8 +3,8 @@
 // cores. Arguments arrive validated by the C ABI entry points.
 //
 // Sparsified MLP (Eq. (1)) over the union U of the batch's neuron sets (Section 5.2):
-//   [union] -> x-hat fp16 -> fc1 on U (MFMA, K-split partials) -> ReLU/bias/mask
-//   -> fc2 on U (MFMA, row-split partials) -> sum + b2 (+ residual).
+//   [union] + x-hat fp16 -> fc1 on U with ReLU/bias/mask (MFMA) -> fc2 on U (MFMA,
+//   row-split partials) -> sum + b2 (+ residual).
 // Sparsified attention (Eq. (2)) with a head set per sequence: the union of the head
 // sets gives the Q/K/V rows read once for the batch; each (sequence, head) pair keeps
 // its own query, cache rows and attention; the out-projection contracts over the
@@ -23,24 +23,21 @@ int batch_nb(int B) { return B <= 16 ? 16 : 32; }
 
 // ---------------------------------------------------------------- MLP
 struct BMlp {
-  _Float16* X16; int32_t* U; int32_t* cnt; uint32_t* mask; float* P; _Float16* C;
+  _Float16* X16; int32_t* U; int32_t* cnt; uint32_t* mask; _Float16* C;
   float* P2;
-  int Kpad, S, Ks, umax, nrows_pad, ldc, S2;
+  int Kpad, umax, ldc, S2;
 };
 
 static size_t bmlp_layout(int d, int n, int B, int n_idx, bool per_seq, Workspace& w, BMlp* o) {
   const int NB = batch_nb(B);
-  o->Kpad = round_up(d, 32);
-  mrows_split(o->Kpad, NB, &o->S, &o->Ks);
+  o->Kpad = round_up(d, 64);
   o->umax = per_seq ? (int)std::min<long>(n, (long)B * n_idx) : n_idx;
-  o->nrows_pad = round_up(std::max(o->umax, 1), 16);
   o->ldc = round_up(std::max(o->umax, 1), 64);
   o->S2 = mcols_split(d, o->umax);
   o->X16 = w.take<_Float16>((size_t)NB * o->Kpad * 2);
   o->U = w.take<int32_t>(per_seq ? (size_t)o->umax * 4 : 0);
   o->cnt = w.take<int32_t>(4);
   o->mask = w.take<uint32_t>(per_seq ? (size_t)o->umax * 4 : 0);
-  o->P = w.take<float>((size_t)o->S * o->nrows_pad * NB * 4);
   o->C = w.take<_Float16>((size_t)NB * o->ldc * 2);
   o->P2 = w.take<float>((size_t)o->S2 * B * d * 4);
   return w.off;
@@ -62,22 +59,17 @@ static dv_status bmlp_run(const dv_mlp* m, const BMlp& o, int B, const int32_t* 
   int list_max = n_idx;
   if (per_seq) {
     if (!union_done)
-      DV_LAUNCH("union", hs, launch_union(idx, B, n_idx, m->n, o.U, o.cnt, masked ? o.mask : nullptr, hs));
+      DV_LAUNCH("union", hs, launch_union(idx, B, n_idx, m->n, o.U, o.cnt, masked ? o.mask : nullptr, nullptr, hs));
     list = o.U;
     list_count = o.cnt;
     list_max = o.umax;
   }
-  MrowsArgs r{};
-  r.d = m->d; r.Kpad = o.Kpad; r.Ks = o.Ks; r.S = o.S; r.X = o.X16; r.mode = kRowsList;
-  r.W0 = m->W1T; r.list = list; r.list_count = list_count; r.list_max = list_max; r.list_range = m->n;
-  r.P = o.P; r.nrows_pad = o.nrows_pad; r.B = B;
-  DV_LAUNCH("fc1", hs, launch_mrows(NB, r, hs));
-  Fc1FinishArgs f{};
-  f.P = o.P; f.S = o.S; f.nrows_pad = o.nrows_pad; f.list = list; f.list_count = list_count;
-  f.list_max = list_max; f.list_range = m->n; f.b1 = m->b1; f.mask = (per_seq && masked) ? o.mask : nullptr; f.B = B;
-  f.act = m->act;
-  f.C = o.C; f.ldc = o.ldc;
-  DV_LAUNCH("fc1_finish", hs, launch_fc1_finish(NB, f, hs));
+  RowsArgs r{};
+  RowsSrc& rs = r.src[0];
+  rs.d = m->d; rs.X = o.X16; rs.W0 = m->W1T; rs.list = list; rs.list_count = list_count; rs.list_max = list_max;
+  rs.list_range = m->n;
+  r.B = B; r.C = o.C; r.b1 = m->b1; r.mask = (per_seq && masked) ? o.mask : nullptr; r.act = m->act;
+  DV_LAUNCH("fc1", hs, launch_rows(NB, kEpiFc1, DV_F32, false, r, hs));
   McolsArgs c{};
   c.d = m->d; c.M = m->W2T; c.list = list; c.list_count = list_count; c.list_max = list_max; c.dh = 0;
   c.list_range = m->n;
@@ -101,7 +93,8 @@ dv_status batch_mlp(const dv_mlp* m, const float* x, int B, const int32_t* idx, 
   const bool masked = batch_mode == DV_MLP_MASKED;
   if (per_seq) {
     DV_LAUNCH("xcast_union", hs, launch_cast_union(x, B, batch_nb(B), m->d, o.Kpad, nullptr, nullptr, 0.f, o.X16, idx,
-                                                   n_idx, m->n, o.U, o.cnt, masked ? o.mask : nullptr, hs));
+                                                   n_idx, m->n, o.U, o.cnt, masked ? o.mask : nullptr, nullptr,
+                                                   hs));
     return bmlp_run(m, o, B, idx, n_idx, true, masked, nullptr, out, hs, true);
   }
   DV_LAUNCH("xcast", hs, launch_ln_cast(x, B, batch_nb(B), m->d, o.Kpad, nullptr, nullptr, 0.f, o.X16, hs));
@@ -110,23 +103,21 @@ dv_status batch_mlp(const dv_mlp* m, const float* x, int B, const int32_t* idx, 
 
 // ---------------------------------------------------------------- attention
 struct BAttn {
-  _Float16* X16; int32_t* Uh; int32_t* hcnt; float* P; float* q; float* part;
+  _Float16* X16; int32_t* Uh; int32_t* hcnt; int32_t* slot; float* q; float* part;
   _Float16* C;
   float* P2;
-  int Kpad, S, Ks, nrows_pad, ldc, S2;
+  int Kpad, ldc, S2;
 };
 
 static size_t battn_layout(const dv_attn* a, int B, int n_heads, Workspace& w, BAttn* o) {
   const int NB = batch_nb(B);
-  o->Kpad = round_up(a->d, 32);
-  mrows_split(o->Kpad, NB, &o->S, &o->Ks);
-  o->nrows_pad = round_up(3 * a->H * a->dh, 16);
+  o->Kpad = round_up(a->d, 64);
   o->ldc = round_up(a->H * a->dh, 64);
   o->S2 = mcols_split(a->d, a->H * a->dh);
   o->X16 = w.take<_Float16>((size_t)NB * o->Kpad * 2);
   o->Uh = w.take<int32_t>((size_t)a->H * 4);
   o->hcnt = w.take<int32_t>(4);
-  o->P = w.take<float>((size_t)o->S * o->nrows_pad * NB * 4);
+  o->slot = w.take<int32_t>((size_t)B * a->H * 4);
   o->q = w.take<float>((size_t)B * std::max(n_heads, 1) * a->dh * 4);
   o->part = w.take<float>((size_t)B * std::max(n_heads, 1) * kAttnMaxSplit * (a->dh + 2) * 4);
   o->C = w.take<_Float16>((size_t)NB * o->ldc * 2);
@@ -153,20 +144,16 @@ static dv_status battn_run(const dv_attn* a, const dv_kv* kv, const BAttn& o, in
     DV_LAUNCH("oproj_finish", hs, launch_cols_finish(e, hs));
     return DV_OK;
   }
-  if (!union_done) DV_LAUNCH("union_heads", hs, launch_union(heads, B, n_heads, a->H, o.Uh, o.hcnt, nullptr, hs));
-  MrowsArgs r{};
-  r.d = a->d; r.Kpad = o.Kpad; r.Ks = o.Ks; r.S = o.S; r.X = o.X16; r.mode = kRowsHeads;
-  r.W0 = a->Wq; r.W1 = a->Wk; r.W2 = a->Wv; r.list = o.Uh; r.list_count = o.hcnt; r.list_max = a->H;
-  r.list_range = a->H;
-  r.dh = a->dh; r.P = o.P; r.nrows_pad = o.nrows_pad; r.B = B;
-  DV_LAUNCH("qkv", hs, launch_mrows(NB, r, hs));
-  QkvFinishArgs qf{};
-  qf.P = o.P; qf.S = o.S; qf.nrows_pad = o.nrows_pad; qf.heads = heads; qf.n_heads = n_heads; qf.H = a->H;
-  qf.dh = a->dh; qf.cap = kv->cap; qf.B = B; qf.hlist = o.Uh; qf.hcount = o.hcnt;
-  qf.bq = a->bq; qf.bk = a->bk; qf.bv = a->bv; qf.q = o.q; qf.K = kv->K; qf.V = kv->V;
+  if (!union_done) DV_LAUNCH("union_heads", hs, launch_union(heads, B, n_heads, a->H, o.Uh, o.hcnt, nullptr, o.slot, hs));
+  RowsArgs r{};
+  RowsSrc& rs = r.src[0];
+  rs.d = a->d; rs.X = o.X16; rs.W0 = a->Wq; rs.W1 = a->Wk; rs.W2 = a->Wv; rs.n0 = a->H * a->dh;
+  rs.list = o.Uh; rs.list_count = o.hcnt; rs.list_max = a->H; rs.list_range = a->H; rs.dh = a->dh;
+  r.B = B; r.slot = o.slot; r.n_heads = n_heads; r.cap = kv->cap;
+  r.bq = a->bq; r.bk = a->bk; r.bv = a->bv; r.q = o.q; r.K = kv->K; r.V = kv->V;
   int maxpos = 0;
   for (int b = 0; b < B; ++b) {
-    qf.posb[b] = kv->pos[b];
+    r.posb[b] = kv->pos[b];
     maxpos = std::max(maxpos, kv->pos[b]);
   }
   AttnArgs at{};
@@ -176,7 +163,7 @@ static dv_status battn_run(const dv_attn* a, const dv_kv* kv, const BAttn& o, in
   at.n_split = (maxpos + 1 + at.chunk - 1) / at.chunk;
   at.q = o.q; at.heads = heads; at.K = kv->K; at.V = kv->V; at.scale = scale; at.part = o.part;
   // One chunk per head (many sequences): the attention writes the coefficients itself,
-  // into a matrix the QKV finisher clears; otherwise a launch combines the chunks.
+  // into a matrix the QKV launch clears; otherwise a launch combines the chunks.
   const bool direct = at.n_split == 1;
   if (direct && B > 1) {
     // Balance the CUs. At up to 4 (sequence, head) workgroups per CU (batch 32 with 32
@@ -200,10 +187,10 @@ static dv_status battn_run(const dv_attn* a, const dv_kv* kv, const BAttn& o, in
     at.reorder = 1;
   }
   if (direct) {
-    qf.zero = o.C; qf.zero_n = NB * o.ldc;
+    r.zero = o.C; r.zero_n = NB * o.ldc;
     at.C = o.C; at.ldc = o.ldc; at.cnb = NB; at.ulist = o.Uh; at.ucount = o.hcnt;
   }
-  DV_LAUNCH("qkv_finish", hs, launch_qkv_finish(NB, kv->ktype, qf, hs));
+  DV_LAUNCH("qkv", hs, launch_rows(NB, kEpiQkv, kv->ktype, false, r, hs));
   DV_LAUNCH("attn", hs, launch_attn(kv->ktype, at, B, hs));
   if (!direct) {
     AttnFinishArgs af{};
@@ -233,7 +220,7 @@ dv_status batch_attn(const dv_attn* a, const float* x, int B, const dv_kv* kv, c
   }
   if (n_heads > 0)
     DV_LAUNCH("xcast_union_heads", hs, launch_cast_union(x, B, batch_nb(B), a->d, o.Kpad, nullptr, nullptr, 0.f, o.X16,
-                                                         heads, n_heads, a->H, o.Uh, o.hcnt, nullptr, hs));
+                                                         heads, n_heads, a->H, o.Uh, o.hcnt, nullptr, o.slot, hs));
   return battn_run(a, kv, o, B, heads, n_heads, scale, nullptr, out, hs, true);
 }
 
@@ -241,8 +228,7 @@ dv_status batch_attn(const dv_attn* a, const float* x, int B, const dv_kv* kv, c
 struct BBlock {
   BAttn at;        // X16 doubles as LN1(y) and, later, LN2(y~)
   BMlp ml;         // shares nothing with `at` (both live for the whole call)
-  _Float16* Hh16; _Float16* Hm16; float* Pp; float* s_h; float* s_m; int32_t* heads; int32_t* idx; float* yt;
-  int ldr0, ldr1, Sp, Ksp, rows_p;
+  _Float16* Hh16; _Float16* Hm16; float* s_h; float* s_m; int32_t* heads; int32_t* idx; float* yt;
 };
 
 static size_t bblock_layout(const dv_attn* a, const dv_mlp* m, const dv_predictor* pa, const dv_predictor* pm,
@@ -250,14 +236,8 @@ static size_t bblock_layout(const dv_attn* a, const dv_mlp* m, const dv_predicto
   const int NB = batch_nb(B);
   battn_layout(a, B, kh, w, &o->at);
   bmlp_layout(m->d, m->n, B, km, true, w, &o->ml);
-  o->ldr0 = round_up(pa->r, 32);
-  o->ldr1 = round_up(pm->r, 32);
-  const int Kpad = round_up(a->d, 32);
-  mrows_split(Kpad, NB, &o->Sp, &o->Ksp);
-  o->rows_p = round_up(pa->r + pm->r, 16);
-  o->Pp = w.take<float>((size_t)o->Sp * o->rows_p * NB * 4);
-  o->Hh16 = w.take<_Float16>((size_t)NB * o->ldr0 * 2);
-  o->Hm16 = w.take<_Float16>((size_t)NB * o->ldr1 * 2);
+  o->Hh16 = w.take<_Float16>((size_t)NB * round_up(pa->r, 64) * 2);
+  o->Hm16 = w.take<_Float16>((size_t)NB * round_up(pm->r, 64) * 2);
   o->s_h = w.take<float>((size_t)B * a->H * 4);
   o->s_m = w.take<float>((size_t)B * m->n * 4);
   o->heads = w.take<int32_t>((size_t)B * kh * 4);
@@ -273,42 +253,42 @@ size_t batch_block_ws(const dv_attn* a, const dv_mlp* m, const dv_predictor* pa,
   return bblock_layout(a, m, pa, pm, B, kh, km, w, &o);
 }
 
-// The largest predictor rank the batched scores stage takes in one K split.
-int batch_max_rank(int B) {
-  int S = 0, Ks = 0;
-  const int unit = 32 * 8;
-  for (int r = unit;; r += unit) {
-    mrows_split(r, batch_nb(B), &S, &Ks);
-    if (S > 1) return r - unit;
-  }
-}
+// The largest predictor rank of a batched layer.
+int batch_max_rank(int B) { return B <= 16 ? 3072 : 1536; }
 
 // Predictor hidden layers (one or two predictors on the same x16) and their scores.
-static dv_status bpredict(const BBlock& o, const _Float16* x16, int d, int B, const dv_predictor* p0, _Float16* h0,
-                          int ld0, float* s0, const dv_predictor* p1, _Float16* h1, int ld1, float* s1,
-                          hipStream_t hs) {
+static dv_status bpredict(const _Float16* x16, int d, int B, const dv_predictor* p0, _Float16* h0, float* s0,
+                          const dv_predictor* p1, _Float16* h1, float* s1, hipStream_t hs) {
   const int NB = batch_nb(B);
-  MrowsArgs r{};
-  r.d = d; r.Kpad = round_up(d, 32); r.Ks = o.Ksp; r.S = o.Sp; r.X = x16; r.mode = kRowsIdentity;
-  r.W0 = p0->AT; r.n0 = p0->r; r.W1 = p1 ? p1->AT : nullptr; r.nrows = p0->r + (p1 ? p1->r : 0);
-  r.P = o.Pp; r.nrows_pad = o.rows_p; r.B = B;
-  DV_LAUNCH("pred_hidden", hs, launch_mrows(NB, r, hs));
-  DV_LAUNCH("pred_hidden_cast", hs, launch_sum_cast(NB, o.Pp, o.Sp, o.rows_p, 0, p0->r, B, h0, ld0, hs));
-  if (p1) DV_LAUNCH("pred_hidden_cast", hs, launch_sum_cast(NB, o.Pp, o.Sp, o.rows_p, p0->r, p1->r, B, h1, ld1, hs));
-  const dv_predictor* ps[2] = {p0, p1};
-  const _Float16* hx[2] = {h0, h1};
-  const int lds[2] = {ld0, ld1};
-  float* sc[2] = {s0, s1};
-  for (int i = 0; i < 2; ++i) {
-    if (ps[i] == nullptr) continue;
-    MrowsArgs q{};
-    q.d = ps[i]->r; q.Kpad = lds[i];
-    mrows_split(q.Kpad, NB, &q.S, &q.Ks);
-    if (q.S != 1) return DV_ERR_UNSUPPORTED;
-    q.X = hx[i]; q.mode = kRowsIdentity; q.W0 = ps[i]->BT; q.n0 = ps[i]->n_out; q.nrows = ps[i]->n_out;
-    q.out0 = sc[i]; q.ld0 = ps[i]->n_out; q.B = B;
-    DV_LAUNCH("pred_scores", hs, launch_mrows(NB, q, hs));
-  }
+  RowsArgs r{};
+  RowsSrc& rs = r.src[0];
+  rs.d = d; rs.X = x16; rs.W0 = p0->AT; rs.n0 = p0->r; rs.W1 = p1 ? p1->AT : nullptr;
+  rs.nrows = p0->r + (p1 ? p1->r : 0);
+  r.B = B; r.C = h0; r.C1 = h1;
+  DV_LAUNCH("pred_hidden", hs, launch_rows(NB, kEpiCoef, DV_F32, false, r, hs));
+  RowsArgs q{};
+  q.B = B;
+  auto source = [&](RowsSrc& src, const dv_predictor* p, const _Float16* h, float* out) {
+    src.d = p->r; src.X = h; src.W0 = p->BT; src.n0 = p->n_out; src.nrows = p->n_out; src.out = out;
+  };
+  source(q.src[0], p0, h0, s0);
+  if (p1) source(q.src[1], p1, h1, s1);
+  DV_LAUNCH("pred_scores", hs, launch_rows(NB, kEpiOut, DV_F32, false, q, hs));
+  return DV_OK;
+}
+
+// Scores of one predictor for up to kMaxBatch fp32 inputs, the products to fp32's precision.
+dv_status batch_scores(const dv_predictor* p, const float* x, int B, int splits, float* hid, float* scores,
+                       hipStream_t hs) {
+  const int NB = batch_nb(B);
+  RowsArgs r{};
+  RowsSrc& rs = r.src[0];
+  rs.d = p->d; rs.X = x; rs.W0 = p->AT; rs.n0 = p->r; rs.nrows = p->r; rs.out = hid;
+  r.B = B; r.S = splits; r.XP = 1;
+  DV_LAUNCH("pred_hidden", hs, launch_rows(NB, kEpiOut, DV_F32, true, r, hs));
+  rs.d = p->r; rs.X = hid; rs.W0 = p->BT; rs.n0 = p->n_out; rs.nrows = p->n_out; rs.out = scores;
+  r.S = 1; r.XP = splits;
+  DV_LAUNCH("pred_scores", hs, launch_rows(NB, kEpiOut, DV_F32, true, r, hs));
   return DV_OK;
 }
 
@@ -329,7 +309,7 @@ dv_status batch_block(const dv_attn* a, const dv_mlp* m, const dv_predictor* pa,
   dv_status st;
   // 1. LN1(y) as fp16; predictors (both in look-ahead mode) and their top-k sets.
   DV_LAUNCH("ln1", hs, launch_ln_cast(x_in, B, NB, a->d, o.at.Kpad, g1, be1, eps, o.at.X16, hs));
-  st = bpredict(o, o.at.X16, a->d, B, pa, o.Hh16, o.ldr0, o.s_h, ahead ? pm : nullptr, o.Hm16, o.ldr1, o.s_m, hs);
+  st = bpredict(o.at.X16, a->d, B, pa, o.Hh16, o.s_h, ahead ? pm : nullptr, o.Hm16, o.s_m, hs);
   if (st != DV_OK) return st;
   DV_LAUNCH("select_heads", hs,
             launch_select(o.s_h, B, a->H, DV_SELECT_TOPK, kh, 0.f, o.heads, kh, nullptr, heads_out, hs));
@@ -344,11 +324,11 @@ dv_status batch_block(const dv_attn* a, const dv_mlp* m, const dv_predictor* pa,
   const bool masked = batch_mode == DV_MLP_MASKED;
   if (ahead)
     DV_LAUNCH("ln2_union", hs, launch_cast_union(o.yt, B, NB, m->d, o.ml.Kpad, g2, be2, eps, o.ml.X16, o.idx, km,
-                                                 m->n, o.ml.U, o.ml.cnt, masked ? o.ml.mask : nullptr, hs));
+                                                 m->n, o.ml.U, o.ml.cnt, masked ? o.ml.mask : nullptr, nullptr, hs));
   else
     DV_LAUNCH("ln2", hs, launch_ln_cast(o.yt, B, NB, m->d, o.ml.Kpad, g2, be2, eps, o.ml.X16, hs));
   if (!ahead) {
-    st = bpredict(o, o.ml.X16, m->d, B, pm, o.Hm16, o.ldr1, o.s_m, nullptr, nullptr, 0, nullptr, hs);
+    st = bpredict(o.ml.X16, m->d, B, pm, o.Hm16, o.s_m, nullptr, nullptr, nullptr, hs);
     if (st != DV_OK) return st;
     DV_LAUNCH("select_mlp", hs,
               launch_select(o.s_m, B, m->n, DV_SELECT_TOPK, km, 0.f, o.idx, km, nullptr, idx_out, hs));

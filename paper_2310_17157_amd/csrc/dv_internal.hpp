@@ -498,39 +498,57 @@ hipError_t launch_fc1(int wtype, const Fc1Args& a, hipStream_t st);
 // ------------------------------------------------ batched (matrix-core) path
 // Union of B ascending sets in [0, n): U ascending, *count and optional membership
 // bits mask[u] (bit b: U[u] is in set b). Needs union_lds_bytes(n) of LDS per
-// workgroup (no scratch memory).
+// workgroup (no scratch memory). slot (optional, [B][n]): i's place in set b, or -1.
 size_t union_lds_bytes(int n);
 hipError_t launch_union(const int32_t* sets, int B, int k, int n, int32_t* U, int32_t* count, uint32_t* mask,
-                        hipStream_t st);
+                        int32_t* slot, hipStream_t st);
 
-// X16[NB][Kpad] = fp16(LN(x)) (g NULL: x), zero rows b >= B and columns k >= d.
+// X16 (coef_index layout, NB rows, Kpad) = fp16(LN(x)) (g NULL: x), zero for b >= B and k >= d.
 hipError_t launch_ln_cast(const float* x, int B, int NB, int d, int Kpad, const float* g, const float* be, float eps,
                           _Float16* X16, hipStream_t st);
 // The cast above and the union of the B sets (launch_union) in one launch.
 hipError_t launch_cast_union(const float* x, int B, int NB, int d, int Kpad, const float* g, const float* be,
                              float eps, _Float16* X16, const int32_t* sets, int k, int n, int32_t* U,
-                             int32_t* count, uint32_t* mask, hipStream_t st);
+                             int32_t* count, uint32_t* mask, int32_t* slot, hipStream_t st);
 
 enum { kRowsList = 0, kRowsHeads = 1, kRowsIdentity = 2 };
 
-// Gathered rows times the token batch on the matrix cores, split over K:
-// P[s][r][b] = sum_{k in split s} W(r)[k] X16[b][k]. Rows: kRowsList W0[list[r]];
-// kRowsHeads r = (m * nu + p) * dh + t -> row list[p] * dh + t of W0/W1/W2 (m = 0, 1, 2);
-// kRowsIdentity r < n0 -> W0[r], else W1[r - n0]. With out0 set (and S == 1) the
-// result goes straight to out0[b][r] (r < n0) / out1[b][r - n0] for b < B.
-struct MrowsArgs {
-  int d, Kpad, Ks, S;
-  const _Float16* X;                 // [NB][Kpad]
-  int mode;
+// Gathered rows times the token batch on the matrix cores, sum_k W(r)[k] X[b][k], and an
+// epilogue per value (row r, token b).
+// Rows: kRowsList W0[list[r]]; kRowsHeads r = (m * nu + p) * dh + t -> row list[p] * dh + t
+// of W0/W1/W2 (m = 0, 1, 2; n0 = rows of a matrix, nu = *list_count); kRowsIdentity r < n0 ->
+// W0[r], else W1[r - n0].
+struct RowsSrc {
+  int d;                             // row length
+  const void* X;                     // fp16 in coef_index layout, zero to a multiple of 64; or fp32 [B][d]
   const void* W0; const void* W1; const void* W2;   // fp16 rows of d elements
   const int32_t* list; const int32_t* list_count; int list_max; int dh;
   int list_range;                    // list entries are clamped to [0, list_range)
-  int nrows, n0;                     // kRowsIdentity: rows in all, rows of W0
-  float* P; int nrows_pad;           // [S][nrows_pad][NB]
-  float* out0; int ld0; float* out1; int ld1; int B;
+  int nrows, n0;                     // nrows: kRowsIdentity, rows in all
+  float* out;                        // kEpiOut: [B][nrows] ([S][B][nrows] with splits)
 };
-void mrows_split(int Kpad, int NB, int* S, int* Ks);
-hipError_t launch_mrows(int NB, const MrowsArgs& a, hipStream_t st);
+enum { kEpiFc1 = 0, kEpiQkv = 1, kEpiCoef = 2, kEpiOut = 3 };
+struct RowsArgs {
+  RowsSrc src[2];                    // src[1].W0 == NULL: one source
+  int G0;                            // set by the launcher
+  int B;
+  int S, XP;                         // fp32 inputs: splits of the contraction; parts [XP][B][d] X is the sum of
+  // kEpiFc1: C(r, b) = fp16(sigma(v + b1[list[r]])), 0 where bit b of mask[r] is clear, and for
+  // the rows to a multiple of 32. kEpiCoef: C(r, b) = fp16(v) of W0's rows, C1 of W1's, zero to
+  // a multiple of 64. (coef_index layout)
+  _Float16* C; _Float16* C1;
+  const float* b1; const uint32_t* mask; int act;
+  // kEpiQkv: v + bias to q[b][j][t] (m = 0) or cache row pos[b] (round to nearest even) where
+  // head list[p] is the j-th of sequence b's set: slot[b][h] = j, else -1 (launch_union)
+  const int32_t* slot; int n_heads; int cap;
+  const float* bq; const float* bk; const float* bv;
+  float* q; void* K; void* V;
+  int posb[kMaxBatch];
+  _Float16* zero; int zero_n;        // optional: halves to clear (multiple of 8, 16-byte aligned)
+};
+constexpr int kRowsMaxSplit = 4;
+int rows_splits(int nrows);          // splits for a fp32-input launch of nrows rows
+hipError_t launch_rows(int NB, int epi, int kvtype, bool xf32, const RowsArgs& a, hipStream_t st);
 
 // Token-batch coefficients times gathered rows, contracted over the rows:
 // P[s][b][c] = sum_{u in split s} C(b, u) M[row(u)][c], row(u) = list[u] (dh == 0) or
@@ -548,23 +566,13 @@ struct McolsArgs {
 int mcols_split(int d, int nmax);
 hipError_t launch_mcols(int NB, const McolsArgs& a, hipStream_t st);
 
-// Coefficient matrices of the contraction over gathered rows (k_mfma_cols' C): blocks of 32
-// rows, each NB tokens x 32 rows row-major, so that the 32 rows one k-step contracts are
+// Coefficient matrices of the contraction over gathered rows (k_mfma_cols' C), and the inputs of
+// the gathered rows (k_rows' X): blocks of 32 rows, each NB tokens x 32 rows row-major, so that the 32 rows one k-step contracts are
 // one contiguous NB * 64-byte piece (a wavefront's coefficient load then covers whole
 // 128-byte lines instead of 64-byte pieces of 16 token rows).
 __host__ __device__ __forceinline__ size_t coef_index(int b, int u, int nb) {
   return ((size_t)(u >> 5) * nb + b) * 32 + (u & 31);
 }
-
-// C(b, u) = fp16(sigma(sum_s P[s][u][b] + b1[list[u]])), masked by membership bits
-// (C in the layout of coef_index).
-struct Fc1FinishArgs {
-  const float* P; int S, nrows_pad;
-  const int32_t* list; const int32_t* list_count; int list_max; int list_range;
-  const float* b1; const uint32_t* mask; int B; int act;
-  _Float16* C; int ldc;
-};
-hipError_t launch_fc1_finish(int NB, const Fc1FinishArgs& a, hipStream_t st);
 
 // out[b][c] = sum_s P[s][b][c] + bias[c] + resid[b][c].
 struct ColsFinishArgs {
@@ -572,22 +580,6 @@ struct ColsFinishArgs {
   const float* bias; const float* resid; float* out;
 };
 hipError_t launch_cols_finish(const ColsFinishArgs& a, hipStream_t st);
-
-// C[b][j] = fp16(sum_s P[s][row0 + j][b]) for j < r, zero padded to [NB][ldc].
-hipError_t launch_sum_cast(int NB, const float* P, int S, int nrows_pad, int row0, int r, int B, _Float16* C, int ldc,
-                           hipStream_t st);
-
-// Q/K/V from kRowsHeads partials: q[b][j][t] and cache rows pos[b] of the selected heads.
-struct QkvFinishArgs {
-  const float* P; int S, nrows_pad;
-  const int32_t* heads; int n_heads, H, dh, cap, B;
-  const int32_t* hlist; const int32_t* hcount;     // union of the head sets and its size
-  const float* bq; const float* bk; const float* bv;
-  float* q; void* K; void* V;
-  int posb[kMaxBatch];
-  _Float16* zero; int zero_n;       // optional: halves to clear (multiple of 8, 16-byte aligned)
-};
-hipError_t launch_qkv_finish(int NB, int kvtype, const QkvFinishArgs& a, hipStream_t st);
 
 // Out-projection coefficients C(b, p*dh + t) (coef_index layout) from the split-KV partials.
 struct AttnFinishArgs {
@@ -600,6 +592,9 @@ hipError_t launch_attn_finish(int NB, const AttnFinishArgs& a, hipStream_t st);
 // Host side of the batched path (dv_batch_api.hip); arguments already validated.
 int batch_nb(int B);
 int batch_max_rank(int B);
+// Scores of one fp16 predictor for up to kMaxBatch fp32 inputs (hid: [splits][B][r]).
+dv_status batch_scores(const dv_predictor* p, const float* x, int B, int splits, float* hid, float* scores,
+                       hipStream_t hs);
 size_t batch_mlp_ws(const dv_mlp* m, int B, int n_idx, int per_seq);
 size_t batch_attn_ws(const dv_attn* a, int B, int n_heads);
 size_t batch_block_ws(const dv_attn* a, const dv_mlp* m, const dv_predictor* pa, const dv_predictor* pm, int B,

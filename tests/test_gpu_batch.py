@@ -54,6 +54,26 @@ def test_batch_mlp_per_sequence_sets(B, mode):
         assert rel_l2(got[b], ref[b]) < REL_TOL, (b, rel_l2(got[b], ref[b]))
 
 
+@pytest.mark.parametrize("B,d,n,k", [(2, 8, 3, 1), (16, 72, 40, 7), (17, 1288, 300, 300), (3, 136, 16, 16),
+                                     (32, 200, 9000, 4000), (5, 4104, 700, 90)])
+@pytest.mark.parametrize("mode", ["union", "masked"])
+def test_batch_mlp_row_and_width_remainders(B, d, n, k, mode):
+    """Row shares of none, one, part of a tile and several rounds of ten tiles per workgroup,
+    and widths of one partial 64-element block to 65 blocks over eight wavefronts."""
+    cfg = get_config("small_b8").with_(name="rem", B=B, d=d, N=n, k_mlp=k, H=2, dh=8, r=8, k_heads=1, L=4, L_range=(4, 4))
+    t = make_layer(cfg, 31, device="cuda", biases=True, with_predictors=False)
+    t["x"] = t["x"] * 50.0
+    sets = zipf_mlp_sets(cfg, 31) if k < n else np.tile(np.arange(n, dtype=np.int32), (B, 1))
+    idx = torch.tensor(sets, dtype=torch.int32, device="cuda")
+    bm = Bd.DV_MLP_UNION if mode == "union" else Bd.DV_MLP_MASKED
+    out = Bd.dv_sparse_mlp(_mlp(t), t["x"], idx, idx_per_seq=1, batch_mode=bm)
+    _sync()
+    m = oracle_mlp(t)
+    ref = O.mlp_batch(host(t["x"]), m["W1T"], m["b1"], m["W2T"], m["b2"], [s.tolist() for s in sets], mode)
+    for b in range(B):
+        assert rel_l2(host(out)[b], ref[b]) < REL_TOL, (b, rel_l2(host(out)[b], ref[b]))
+
+
 @pytest.mark.parametrize("offset", [1, 2, 3])
 @pytest.mark.parametrize("mode", ["union", "masked"])
 def test_batch_mlp_sets_at_any_word_offset(offset, mode):

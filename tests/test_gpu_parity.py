@@ -76,6 +76,58 @@ def test_predict_batch_rows_are_independent():
         check_topk_set(host(idx)[b], s_or, cfg.k_mlp)
 
 
+@pytest.mark.parametrize("B,d,r,n", [(2, 8, 8, 3), (3, 72, 24, 40), (16, 1288, 200, 5000), (17, 392, 40, 1000),
+                                     (33, 4104, 1000, 4100), (5, 12288, 1016, 131)])
+def test_predict_batch_scores_to_fp32(B, d, r, n):
+    """A batch on fp16 factors runs on the matrix cores with the inputs split into three
+    fp16 terms: scores as exact as fp32 arithmetic, for inputs of any scale (rows scaled by
+    1e-20 to 1e15, and rows whose elements span 2^-40 to 1), whole tiles and remainders of rows, of
+    the contraction and of the batch (more than 32 inputs run in turns). The bound: a
+    result rounded to fp32 in each layer and in each of up to four parts of the hidden layer, with partial
+    sums of 128 terms rounded four times, is within 3e-7 in relative L2."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B * 1000 + d)
+    rnd = lambda *sh: torch.randn(sh, generator=g, device="cuda")
+    pred = Bd.Predictor((0.02 * rnd(r, d)).half(), (0.02 * rnd(n, r)).half())
+    x = rnd(B, d)
+    x[0] *= 1e-20
+    x[1] *= 1e15
+    if B > 2:
+        x[2] *= torch.exp2(-40.0 * torch.rand(d, generator=g, device="cuda"))
+    sc = torch.empty((B, n), dtype=torch.float32, device="cuda")
+    ref = (x.double() @ pred.AT.double().T) @ pred.BT.double().T
+    nb = Bd.predict_workspace_bytes(pred, B)
+    one_part = 256 * ((B * r * 4 + 255) // 256) + 256 * ((B * n * 4 + 255) // 256)
+    for size in {nb, min(nb, one_part)}:          # (with less scratch the hidden layer is one part)
+        sc.fill_(float("nan"))
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        Bd.dv_predict_mlp(pred, x, min(n, 5), scores=sc, ws=ws)
+        _sync()
+        for b in range(B):
+            err = float((sc[b].double() - ref[b]).norm() / ref[b].norm())
+            assert err < 3e-7, (size, b, err)
+
+
+def test_predict_batch_infinities_stay_in_their_row():
+    """An infinite or NaN input makes its own row's scores non-finite and no other's."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    pred = Bd.Predictor(torch.randn((40, 392), generator=g, device="cuda").half(),
+                        torch.randn((70, 40), generator=g, device="cuda").half())
+    x = torch.randn((6, 392), generator=g, device="cuda")
+    clean = torch.empty((6, 70), dtype=torch.float32, device="cuda")
+    Bd.dv_predict_mlp(pred, x, 1, scores=clean)
+    x[1, 7], x[4, 390] = float("inf"), float("nan")
+    sc = torch.empty_like(clean)
+    Bd.dv_predict_mlp(pred, x, 1, scores=sc)
+    _sync()
+    for b in range(6):
+        if b in (1, 4):
+            assert not torch.isfinite(sc[b]).any()
+        else:
+            assert torch.equal(sc[b], clean[b])
+
+
 def test_topk_ties_and_edge_sizes():
     """Exact ties in the scores: lower index first. k = n and k = 0 edge sizes."""
     d, r, n = 64, 8, 300

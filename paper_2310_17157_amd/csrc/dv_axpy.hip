@@ -241,6 +241,8 @@ __global__ void __launch_bounds__(256) k_axpy_sum(AxpyArgs a, int S) {
   if (a.out2) *reinterpret_cast<f32x4*>(a.out2 + i) = v;
 }
 
+constexpr int kAxpyWholeRows = 512;   // rows up to which a column tile is not split over rows
+
 // Row splits: enough workgroups to give every CU one, each split at least two groups
 // of rows per wavefront; one split when there is no partial buffer.
 static int axpy_row_splits(int spans, int nrows, int rows_per_round) {
@@ -250,11 +252,11 @@ static int axpy_row_splits(int spans, int nrows, int rows_per_round) {
 }
 
 template <typename T, bool HEADS, int NW = kAxNW, int U = kAxU, int R = 1>
-static hipError_t launch_axpy_t(AxpyArgs a, hipStream_t st) {
+static hipError_t launch_axpy_t(AxpyArgs a, hipStream_t st, bool whole = false) {
   constexpr int E = Chunk<T>::E;
   constexpr int LR = 64 / R;
   const int spans = (a.d / E + LR - 1) / LR;
-  const int S = a.partial != nullptr ? axpy_row_splits(spans, a.nrows, NW * R) : 1;
+  const int S = a.partial != nullptr && !whole ? axpy_row_splits(spans, a.nrows, NW * R) : 1;
   if (spans > kAxpyMaxSpans) a.cnt = nullptr;   // no counter per span: the split sum is a launch
   // LDS: (coefficient, row index) pairs of a batch of the split's rows and the
   // wavefront sums.
@@ -272,6 +274,17 @@ hipError_t launch_axpy(int wtype, const AxpyArgs& a, hipStream_t st) {
   // against the 2048-column spans of one row per load with a separate split-sum
   // launch; batches of 4 and 8, and 4 wavefronts, were slower)
   if (wtype == DV_Q4) return a.dh > 0 ? hipErrorInvalidValue : launch_axpy_t<q4_t, false, 8, 2, 4>(a, st);
+  // Few rows: a workgroup per 128-byte column tile takes all of them (8 rows per load), so no
+  // split sum follows, whose stores, ticket and reads are a chain of about 2 us: 256 fp32 head
+  // rows of 768 columns 7.5 -> 5.4 us, 307 neuron rows 5.3 -> 4.5. With more rows the tiles are too
+  // few and long (4096 columns: 1536 head rows 10.8 -> 14.6 us).
+  if (a.nrows > 0 && a.nrows <= kAxpyWholeRows) {
+    if (a.dh > 0)
+      return wtype == DV_F16 ? launch_axpy_t<_Float16, true, 8, 4, 8>(a, st, true)
+                             : launch_axpy_t<float, true, 8, 4, 8>(a, st, true);
+    return wtype == DV_F16 ? launch_axpy_t<_Float16, false, 8, 4, 8>(a, st, true)
+                           : launch_axpy_t<float, false, 8, 4, 8>(a, st, true);
+  }
   if (a.dh > 0)
     return wtype == DV_F16 ? launch_axpy_t<_Float16, true>(a, st) : launch_axpy_t<float, true>(a, st);
   return wtype == DV_F16 ? launch_axpy_t<_Float16, false>(a, st) : launch_axpy_t<float, false>(a, st);

@@ -48,12 +48,12 @@ __global__ void __launch_bounds__(NW * 64) k_fc1(Fc1Args a) {
                                 gridDim.x, tail, scale_ptr);
 }
 
-template <typename T, int KX>
+template <typename T, int KX, int NW = 16>
 static hipError_t launch_fc1_t(const Fc1Args& a, hipStream_t st) {
   // two batches of 2 loads in flight per wavefront: measured faster than all of a
   // wavefront's loads at once (12 at the OPT-175B shape) or batches of 1, 3, 4 or 6,
   // as deeper queues let the XCDs that win the fabric arbitration run ahead
-  constexpr int NW = 16, U = 2;
+  constexpr int U = 2;
   const int blocks = max(1, min(a.k, device_cu_count()));
   const size_t lds = (size_t)(a.d + NW + rowdot_flat_part(a.k, blocks, NW)) * sizeof(float);
   const void* kern = a.g != nullptr ? reinterpret_cast<const void*>(k_fc1<T, NW, U, KX, true>)
@@ -69,6 +69,16 @@ static hipError_t launch_fc1_t(const Fc1Args& a, hipStream_t st) {
 
 template <typename T>
 static hipError_t launch_fc1_k(const Fc1Args& a, hipStream_t st) {
+  if constexpr (!kIsQ4<T>) {
+    if (rowdot_small(a.k, a.d, Chunk<T>::E)) {
+      switch (rowdot_kx(a.d, 4)) {
+        case 1: return launch_fc1_t<T, 1, 4>(a, st);
+        case 2: return launch_fc1_t<T, 2, 4>(a, st);
+        case 3: return launch_fc1_t<T, 3, 4>(a, st);
+        default: return launch_fc1_t<T, 4, 4>(a, st);
+      }
+    }
+  }
   switch (rowdot_kx(a.d, 16)) {
     case 1: return launch_fc1_t<T, 1>(a, st);
     case 2: return launch_fc1_t<T, 2>(a, st);

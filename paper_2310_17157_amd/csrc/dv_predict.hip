@@ -31,12 +31,12 @@ __global__ void __launch_bounds__(NW * 64) k_pred_hidden(PredHidArgs a) {
                         a.xhat_out ? a.xhat_out + (size_t)b * a.d : nullptr, blockIdx.x, gridDim.x);
 }
 
-template <typename T, int KX>
+template <typename T, int KX, int NW = 16>
 static hipError_t launch_pred_hidden_t(const PredHidArgs& a, hipStream_t st) {
   // two batches of 2 loads in flight per wavefront: measured faster than all of a
   // wavefront's loads at once (12 at the OPT-175B shape) or batches of 1, 3, 4 or 6,
   // as deeper queues let the XCDs that win the fabric arbitration run ahead
-  constexpr int NW = 16, U = 2;
+  constexpr int U = 2;
   const int nrows = a.r0 + a.r1;
   const dim3 grid(max(1, min(nrows, device_cu_count())), a.B);
   const size_t lds = (size_t)(a.d + NW + rowdot_flat_part(nrows, grid.x, NW)) * sizeof(float);
@@ -53,6 +53,14 @@ static hipError_t launch_pred_hidden_t(const PredHidArgs& a, hipStream_t st) {
 
 template <typename T>
 static hipError_t launch_pred_hidden_k(const PredHidArgs& a, hipStream_t st) {
+  if (rowdot_small(a.r0 + a.r1, a.d, Chunk<T>::E)) {
+    switch (rowdot_kx(a.d, 4)) {
+      case 1: return launch_pred_hidden_t<T, 1, 4>(a, st);
+      case 2: return launch_pred_hidden_t<T, 2, 4>(a, st);
+      case 3: return launch_pred_hidden_t<T, 3, 4>(a, st);
+      default: return launch_pred_hidden_t<T, 4, 4>(a, st);
+    }
+  }
   switch (rowdot_kx(a.d, 16)) {
     case 1: return launch_pred_hidden_t<T, 1>(a, st);
     case 2: return launch_pred_hidden_t<T, 2>(a, st);

@@ -176,6 +176,16 @@ __device__ __forceinline__ void rowdot_flat(RowPtr row_ptr, Epi epi, int nrows, 
 // Smallest KX for a row of d floats with NW wavefronts (at most 4).
 inline int rowdot_kx(int d, int nw) { return (d + 256 * nw - 1) / (256 * nw); }
 
+// Whether a launch's workgroups (one per CU at most) take 4 wavefronts instead of 16: rows up to
+// 4096 floats (4 float4 of the input per thread) and at most 48 load slots per workgroup. Fewer
+// wavefronts are dispatched, stage and meet at barriers sooner; more slots want more loads in
+// flight. fc1 of 307 rows of 768 fp32 6.7 -> 5.2 us, 501 of 1288 fp16 6.2 -> 5.2, 1310 of 4096
+// fp16 (41 slots) 9.0 -> 8.3; predictor of 128 rows of 768 fp32 6.0 -> 4.4. (Two workgroups per CU: the same.)
+inline bool rowdot_small(int nrows, int d, int elems) {
+  const long slots = (long)nrows * ((d / elems + 63) / 64);
+  return rowdot_kx(d, 4) <= 4 && slots <= 48L * device_cu_count();
+}
+
 // LDS floats rowdot_flat needs for its per-wavefront records.
 inline int rowdot_flat_part(int nrows, int G, int nw) { return nw * ((nrows + G - 1) / G + 1); }
 

@@ -280,6 +280,26 @@ def test_sparse_mlp(name):
     assert rel_l2(host(out)[0], ref) < REL_TOL
 
 
+@pytest.mark.parametrize("wd", ["f16", "f32"])
+@pytest.mark.parametrize("d,k", [(8, 1), (72, 9), (1288, 511), (1288, 512), (1288, 513), (1032, 1531), (4096, 1536),
+                                 (4096, 1537), (4104, 300)])
+def test_sparse_mlp_workgroup_shape_edges(wd, d, k):
+    """Both sides of the lines where the row-dot takes 4 or 16 wavefronts (4096 floats, 48 load
+    slots per workgroup) and the row-axpy takes a column tile whole or splits its rows (512 rows), and
+    the smallest sizes."""
+    cfg = get_config("small_f16").with_(name="edges", d=d, N=max(2 * k, 4), k_mlp=k, H=2, dh=8, r=8, L=4, wdtype=wd)
+    _, t = layer(cfg, 33, biases=True, with_predictors=False)
+    rng = np.random.default_rng(34)
+    idx = np.sort(rng.permutation(cfg.N)[:k]).astype(np.int32)
+    x = torch.randn((1, d), device="cuda")
+    out = Bd.dv_sparse_mlp(Bd.MLP(t["W1T"], t["W2T"], t["b1"], t["b2"]), x, torch.tensor(idx, device="cuda"))
+    _sync()
+    m = oracle_mlp(t)
+    ref = O.mlp_sparse(host(x)[0], m["W1T"], m["b1"], m["W2T"], m["b2"], idx)
+    # fp32 sums of up to 4104 and 1537 products in trees: well inside 2e-6
+    assert rel_l2(host(out)[0], ref) < 2e-6
+
+
 def test_sparse_mlp_full_set_is_dense_and_empty_set_is_bias():
     cfg, t = layer("small_f16", 22, biases=True)
     _, mlp, *_ = layer_objects(t, cfg.H)

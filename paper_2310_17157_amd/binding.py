@@ -178,6 +178,23 @@ def _tensor(name, t, dtypes, ndim=None, shape=None, optional=False, dev=True):
         _gpu(name, t)
 
 
+def _fits(t, dtype, shape) -> bool:
+    """Whether t is a plain GPU tensor of this dtype and shape, contiguous: the usual case, in
+    a third of the full checks' time (an entry point whose arguments all fit skips them)."""
+    return type(t) is torch.Tensor and t.dtype is dtype and t.shape == shape and t.is_cuda and t.is_contiguous()
+
+
+def _fits_rows(t, width) -> bool:
+    """_fits for an fp32 input of any number of rows."""
+    return (type(t) is torch.Tensor and t.dtype is torch.float32 and t.dim() == 2 and t.shape[1] == width and t.is_cuda
+            and t.is_contiguous())
+
+
+def _fits_set(t) -> bool:
+    """_fits for an int32 index set of any shape."""
+    return type(t) is torch.Tensor and t.dtype is torch.int32 and t.is_cuda and t.is_contiguous()
+
+
 def _gpu(name, *ts):
     for t in ts:
         if t is not None and t.device.type != "cuda":
@@ -186,7 +203,8 @@ def _gpu(name, *ts):
 
 def _wsarg(ws):
     """(pointer, bytes) of a workspace: a contiguous uint8 GPU tensor."""
-    _tensor("ws", ws, (torch.uint8,), 1)
+    if not (type(ws) is torch.Tensor and ws.dtype is torch.uint8 and ws.dim() == 1 and ws.is_cuda and ws.is_contiguous()):
+        _tensor("ws", ws, (torch.uint8,), 1)
     return ws.data_ptr(), ws.numel()
 
 
@@ -196,8 +214,13 @@ def _same_dtype(name, *ts):
         raise TypeError(f"{name}: all weights must share one dtype, got {sorted(str(d) for d in ds)}")
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch._C._cuda_getDevice())   # (1.5 us less than a Stream object)
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -373,12 +396,16 @@ def _predict(fn, pred: Predictor, x, k=0, mode=DV_SELECT_TOPK, thresh=0.0, idx=N
              scores=None, cap_idx=None, ws=None, flags=0, stream=None):
     lib = load()
     cp = pred.c()
-    _tensor("x", x, _F32, 2, (None, cp.d), dev=False)
+    if not (_fits_rows(x, cp.d) and (idx is None or (_fits_set(idx) and idx.dim() == 2 and idx.shape[0] == x.shape[0]))
+            and (count is None or _fits(count, torch.int32, (x.shape[0],)))
+            and (scores is None or _fits(scores, torch.float32, (x.shape[0], cp.n_out)))):
+        _tensor("x", x, _F32, 2, (None, cp.d), dev=False)
+        B = x.shape[0]
+        _tensor("idx", idx, _I32, 2, (B, None), optional=True, dev=False)
+        _tensor("count", count, _I32, 1, (B,), optional=True, dev=False)
+        _tensor("scores", scores, _F32, 2, (B, cp.n_out), optional=True, dev=False)
+        _gpu("arguments", x, idx, count, scores)
     B = x.shape[0]
-    _tensor("idx", idx, _I32, 2, (B, None), optional=True, dev=False)
-    _tensor("count", count, _I32, 1, (B,), optional=True, dev=False)
-    _tensor("scores", scores, _F32, 2, (B, cp.n_out), optional=True, dev=False)
-    _gpu("arguments", x, idx, count, scores)
     if cap_idx is None:
         cap_idx = k if mode == DV_SELECT_TOPK else cp.n_out
     if idx is None:
@@ -408,14 +435,17 @@ def dv_sparse_mlp(mlp: MLP, x, idx, idx_per_seq=0, batch_mode=DV_MLP_UNION, out=
     """out[b] = MLP_S(x[b]) (Eq. (1)), without residual."""
     lib = load()
     cm = mlp.c()
-    _tensor("x", x, _F32, 2, (None, cm.d), dev=False)
+    fits = _fits_rows(x, cm.d) and _fits_set(idx) and (out is None or _fits(out, torch.float32, x.shape))
+    if not fits:
+        _tensor("x", x, _F32, 2, (None, cm.d), dev=False)
+        _tensor("idx", idx, _I32, dev=False)
     B = x.shape[0]
-    _tensor("idx", idx, _I32, dev=False)
     n_idx = idx.shape[-1]
     if idx_per_seq and idx.numel() != B * n_idx:
         raise ValueError(f"idx holds {idx.numel()} entries; per-sequence sets need B x n_idx = {B * n_idx}")
-    _tensor("out", out, _F32, 2, (B, cm.d), optional=True, dev=False)
-    _gpu("arguments", x, idx, out)
+    if not fits:
+        _tensor("out", out, _F32, 2, (B, cm.d), optional=True, dev=False)
+        _gpu("arguments", x, idx, out)
     if out is None:
         out = torch.empty((B, cm.d), dtype=torch.float32, device=x.device)
     if ws is None:
@@ -430,14 +460,17 @@ def dv_sparse_attn(attn: Attn, x, kv: KVCache, heads, scale, out=None, ws=None, 
     """out[b] = bo + sum_{i in S_A^b} H_i(x[b]) W^O_i (Eq. (2)); updates the cache rows at pos."""
     lib = load()
     ca, ck = attn.c(), kv.c()
-    _tensor("x", x, _F32, 2, (None, ca.d), dev=False)
+    fits = _fits_rows(x, ca.d) and _fits_set(heads) and (out is None or _fits(out, torch.float32, x.shape))
+    if not fits:
+        _tensor("x", x, _F32, 2, (None, ca.d), dev=False)
+        _tensor("heads", heads, _I32, dev=False)
     B = x.shape[0]
-    _tensor("heads", heads, _I32, dev=False)
     n_heads = heads.shape[-1]
     if heads.numel() != B * n_heads:
         raise ValueError(f"heads holds {heads.numel()} entries; expected B x n_heads = {B * n_heads}")
-    _tensor("out", out, _F32, 2, (B, ca.d), optional=True, dev=False)
-    _gpu("arguments", x, heads, out)
+    if not fits:
+        _tensor("out", out, _F32, 2, (B, ca.d), optional=True, dev=False)
+        _gpu("arguments", x, heads, out)
     if out is None:
         out = torch.empty((B, ca.d), dtype=torch.float32, device=x.device)
     if ws is None:
@@ -453,11 +486,13 @@ def dv_sparse_mlp_q4(mlp: MLPQ4, x, idx, out=None, ws=None, flags=0, stream=None
     """out = MLP_S(x) with 4-bit weights (Section 5.2, W4A16), one token."""
     lib = load()
     cm = mlp.c()
-    _tensor("x", x, _F32, 2, (1, cm.d), dev=False)
-    _tensor("idx", idx, _I32, dev=False)
+    shape = (1, cm.d)
+    if not (_fits(x, torch.float32, shape) and _fits_set(idx) and (out is None or _fits(out, torch.float32, shape))):
+        _tensor("x", x, _F32, 2, (1, cm.d), dev=False)
+        _tensor("idx", idx, _I32, dev=False)
+        _tensor("out", out, _F32, 2, (1, cm.d), optional=True, dev=False)
+        _gpu("arguments", x, idx, out)
     n_idx = idx.shape[-1]
-    _tensor("out", out, _F32, 2, (1, cm.d), optional=True, dev=False)
-    _gpu("arguments", x, idx, out)
     if out is None:
         out = torch.empty((1, cm.d), dtype=torch.float32, device=x.device)
     if ws is None:
@@ -476,15 +511,21 @@ def dv_sparse_attn_kvfill(attn: Attn, x, kv: KVCache, Y, valid, heads, scale, ou
     (both updated in place)."""
     lib = load()
     ca, ck = attn.c(), kv.c()
-    _tensor("x", x, _F32, 2, (1, ca.d), dev=False)
-    _tensor("Y", Y, (kv.K.dtype,), 2, (ck.cap, ca.d), dev=False)
-    _tensor("valid", valid, (torch.uint8,), 2, (ca.H, ck.cap), dev=False)
-    _tensor("heads", heads, _I32, dev=False)
+    shape = (1, ca.d)
+    fits = (_fits(x, torch.float32, shape) and _fits(Y, kv.K.dtype, (ck.cap, ca.d))
+            and _fits(valid, torch.uint8, (ca.H, ck.cap)) and _fits_set(heads)
+            and (out is None or _fits(out, torch.float32, shape)))
+    if not fits:
+        _tensor("x", x, _F32, 2, (1, ca.d), dev=False)
+        _tensor("Y", Y, (kv.K.dtype,), 2, (ck.cap, ca.d), dev=False)
+        _tensor("valid", valid, (torch.uint8,), 2, (ca.H, ck.cap), dev=False)
+        _tensor("heads", heads, _I32, dev=False)
     n_heads = heads.shape[-1]
     if heads.numel() != n_heads:
         raise ValueError("heads: one sequence's set")
-    _tensor("out", out, _F32, 2, (1, ca.d), optional=True, dev=False)
-    _gpu("arguments", x, Y, valid, heads, out)
+    if not fits:
+        _tensor("out", out, _F32, 2, (1, ca.d), optional=True, dev=False)
+        _gpu("arguments", x, Y, valid, heads, out)
     if out is None:
         out = torch.empty((1, ca.d), dtype=torch.float32, device=x.device)
     if ws is None:
@@ -502,12 +543,16 @@ def dv_sparse_block(attn: Attn, mlp: MLP, pred_h: Predictor, pred_m: Predictor, 
     lib = load()
     ca, cm, cph, cpm, ck = attn.c(), mlp.c(), pred_h.c(), pred_m.c(), kv.c()
     cl = ln.c() if ln is not None else None
-    _tensor("x", x, _F32, 2, (None, ca.d), dev=False)
+    if not (_fits_rows(x, ca.d) and (out is None or _fits(out, torch.float32, x.shape))
+            and (heads_out is None or _fits(heads_out, torch.int32, (x.shape[0], k_heads)))
+            and (idx_out is None or _fits(idx_out, torch.int32, (x.shape[0], k_mlp)))):
+        _tensor("x", x, _F32, 2, (None, ca.d), dev=False)
+        B = x.shape[0]
+        _tensor("out", out, _F32, 2, (B, ca.d), optional=True, dev=False)
+        _tensor("heads_out", heads_out, _I32, 2, (B, k_heads), optional=True, dev=False)
+        _tensor("idx_out", idx_out, _I32, 2, (B, k_mlp), optional=True, dev=False)
+        _gpu("arguments", x, out, heads_out, idx_out)
     B = x.shape[0]
-    _tensor("out", out, _F32, 2, (B, ca.d), optional=True, dev=False)
-    _tensor("heads_out", heads_out, _I32, 2, (B, k_heads), optional=True, dev=False)
-    _tensor("idx_out", idx_out, _I32, 2, (B, k_mlp), optional=True, dev=False)
-    _gpu("arguments", x, out, heads_out, idx_out)
     if out is None:
         out = torch.empty_like(x)
     if heads_out is None:

@@ -340,6 +340,22 @@ inline void launch_k(void (*kern)(P...), dim3 grid, dim3 block, size_t lds, hipS
 hipError_t launch_select(const float* scores, int B, int n, int mode, int k, float thresh,
                          int32_t* idx, int cap, int32_t* count, int32_t* idx2, hipStream_t st);
 
+// A batch's head sets (top-k of each row of s [B][H]) and their union (launch_union's U, count
+// and slot) by one workgroup, whose work per key is H: up to 256 heads and the keys that fit
+// its LDS.
+struct HeadSets {
+  const float* s; int B, H, k;
+  int32_t* sets; int32_t* sets2;     // [B][k], ascending; sets2 may be NULL
+  int32_t* U; int32_t* count; int32_t* slot;
+};
+constexpr int kHeadSetKeys = 8192, kHeadSetBits = 512;   // words of LDS
+inline bool head_sets_fit(int B, int H) {
+  return H <= 256 && B * H <= kHeadSetKeys && B * ((H >> 5) + 1) <= kHeadSetBits;
+}
+// They and (n > 0) the top-k sets of scores [B][n] in one launch.
+hipError_t launch_select_heads(const HeadSets& heads, const float* scores, int n, int k, int32_t* idx, int32_t* idx2,
+                               hipStream_t st);
+
 // Device-side check that each of B sets set[b][0..n) is strictly ascending within
 // [0, range); writes 0 (valid) or 1 to *bad.
 hipError_t launch_validate_sets(const int32_t* set, int B, int n, int range, int32_t* bad, hipStream_t st);

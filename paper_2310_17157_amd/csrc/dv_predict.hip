@@ -293,11 +293,19 @@ hipError_t launch_pred_scores(int wtype, const PredScoreArgs& a, hipStream_t st)
 // ---------------------------------------------------------------- select
 // IPT: register slots per thread (wg_select_reg); 0: short vectors, ranked in LDS; -1:
 // streamed from memory. A kernel each: inlined side by side, the forms spill.
-template <int IPT, bool PAD>
+// HEADS: the last workgroup makes a batch's head sets instead (IPT = 0 takes that of n == 0).
+template <int IPT, bool PAD, bool HEADS>
 __global__ void __launch_bounds__(1024) k_select(const float* s, int n, int mode, int k, float thresh,
-                                                 int32_t* idx, int cap, int32_t* count, int32_t* idx2) {
-  __shared__ uint32_t hist[IPT == 0 ? 1024 : kSelBins];
+                                                 int32_t* idx, int cap, int32_t* count, int32_t* idx2, HeadSets heads) {
+  __shared__ uint32_t hist[IPT == 0 && !HEADS ? 1024 : kSelBins];
   __shared__ int sm[kSelSm(1024)];
+  if constexpr (HEADS) {
+    __shared__ uint32_t bits[kHeadSetBits];
+    if (blockIdx.x == gridDim.x - 1) {
+      wg_head_sets<1024>(heads, hist, bits, sm);
+      return;
+    }
+  }
   const int b = blockIdx.x;
   const float* sb = s + (size_t)b * n;
   int32_t* ob = idx + (size_t)b * cap;
@@ -311,24 +319,36 @@ __global__ void __launch_bounds__(1024) k_select(const float* s, int n, int mode
     wg_select<1024>(sb, n, mode, k, thresh, ob, cap, cb, ob2, hist, sm);
 }
 
-template <int IPT>
-static hipError_t launch_select_reg(dim3 grid, const float* scores, int n, int mode, int k, float thresh, int32_t* idx,
-                                    int cap, int32_t* count, int32_t* idx2, hipStream_t st) {
+template <int IPT, bool HEADS>
+static void launch_select_reg(dim3 grid, const float* scores, int n, int mode, int k, float thresh, int32_t* idx,
+                              int cap, int32_t* count, int32_t* idx2, const HeadSets& heads, hipStream_t st) {
   if constexpr (IPT > 4)
     if (n <= 1024 * (IPT - 4))
-      return launch_select_reg<IPT - 4>(grid, scores, n, mode, k, thresh, idx, cap, count, idx2, st);
-  launch_k(n == 1024 * IPT ? k_select<IPT, false> : k_select<IPT, true>, grid, dim3(1024), 0, st, scores, n, mode, k,
-           thresh, idx, cap, count, idx2);
+      return launch_select_reg<IPT - 4, HEADS>(grid, scores, n, mode, k, thresh, idx, cap, count, idx2, heads, st);
+  launch_k(n == 1024 * IPT ? k_select<IPT, false, HEADS> : k_select<IPT, true, HEADS>, grid, dim3(1024), 0, st, scores,
+           n, mode, k, thresh, idx, cap, count, idx2, heads);
+}
+
+template <bool HEADS>
+static hipError_t launch_select_h(int rows, const float* scores, int n, int mode, int k, float thresh, int32_t* idx,
+                                  int cap, int32_t* count, int32_t* idx2, const HeadSets& heads, hipStream_t st) {
+  const dim3 grid(rows + (HEADS ? 1 : 0));
+  if (n > 1024 && n <= 1024 * kSelIPT)
+    launch_select_reg<kSelIPT, HEADS>(grid, scores, n, mode, k, thresh, idx, cap, count, idx2, heads, st);
+  else
+    launch_k(n <= 1024 ? k_select<0, false, HEADS> : k_select<-1, false, HEADS>, grid, dim3(1024), 0, st, scores, n,
+             mode, k, thresh, idx, cap, count, idx2, heads);
   return hipGetLastError();
 }
 
 hipError_t launch_select(const float* scores, int B, int n, int mode, int k, float thresh,
                          int32_t* idx, int cap, int32_t* count, int32_t* idx2, hipStream_t st) {
-  if (n > 1024 && n <= 1024 * kSelIPT)
-    return launch_select_reg<kSelIPT>(dim3(B), scores, n, mode, k, thresh, idx, cap, count, idx2, st);
-  launch_k(n <= 1024 ? k_select<0, false> : k_select<-1, false>, dim3(B), dim3(1024), 0, st, scores, n, mode, k, thresh,
-           idx, cap, count, idx2);
-  return hipGetLastError();
+  return launch_select_h<false>(B, scores, n, mode, k, thresh, idx, cap, count, idx2, HeadSets{}, st);
+}
+
+hipError_t launch_select_heads(const HeadSets& heads, const float* scores, int n, int k, int32_t* idx, int32_t* idx2,
+                               hipStream_t st) {
+  return launch_select_h<true>(n > 0 ? heads.B : 0, scores, n, DV_SELECT_TOPK, k, 0.f, idx, k, nullptr, idx2, heads, st);
 }
 
 // One workgroup checks every set: strictly ascending and within [0, range).

@@ -21,6 +21,7 @@
 namespace dv {
 
 constexpr int kSelBins = 8192;   // LDS histogram bins (13-bit digits)
+static_assert(kHeadSetKeys <= kSelBins, "a batch's head scores share the histogram's LDS");
 
 // Scratch ints needed by the selection routines for an NT-thread workgroup.
 constexpr int kSelSm(int NT) { return 2 * (NT / 64) + 8; }
@@ -489,6 +490,48 @@ __device__ void wg_select_small(const float* __restrict__ s, int n, int mode, in
 // wavefront has a share of a short vector: with 48 slots the first wavefront alone would
 // hold 3072 scores and walk them serially.
 constexpr int kSelIPT = 48;
+
+// The head sets of a batch by one workgroup: for each of B rows of H scores the k highest (ties
+// to the lower index, k >= H: every head) by rank counting, and from the sets their union, its
+// size and every head's place in each set (launch_union's outputs). keys: B * H words of LDS;
+// bits: B * (H / 32 + 1) words. Called by the whole workgroup.
+template <int NT>
+__device__ __forceinline__ void wg_head_sets(const HeadSets& a, uint32_t* keys, uint32_t* bits, int* red) {
+  const int tid = threadIdx.x, n = a.B * a.H, words = (a.H >> 5) + 1;
+  for (int e = tid; e < n; e += NT) keys[e] = fkey(a.s[e]);
+  for (int i = tid; i < a.B * words; i += NT) bits[i] = 0u;
+  __syncthreads();
+  for (int e = tid; e < n; e += NT) {
+    const int b = e / a.H, h = e - b * a.H;
+    const uint32_t ki = keys[e];
+    int rank = 0;
+    for (int j = 0; j < a.H; ++j) {
+      const uint32_t kj = keys[b * a.H + j];
+      rank += (kj > ki) || (kj == ki && j < h);
+    }
+    if (rank < a.k) atomicOr(&bits[b * words + (h >> 5)], 1u << (h & 31));
+  }
+  __syncthreads();
+  for (int e = tid; e < n; e += NT) {
+    const int b = e / a.H, h = e - b * a.H;
+    const uint32_t* w = bits + b * words;
+    const bool on = (w[h >> 5] >> (h & 31)) & 1u;
+    int p = __popc(w[h >> 5] & ((1u << (h & 31)) - 1u));
+    for (int i = 0; i < (h >> 5); ++i) p += __popc(w[i]);
+    a.slot[e] = on ? p : -1;
+    if (on) {
+      a.sets[b * a.k + p] = h;
+      if (a.sets2) a.sets2[b * a.k + p] = h;
+    }
+  }
+  bool any = false;
+  if (tid < a.H)
+    for (int b = 0; b < a.B; ++b) any |= (bits[b * words + (tid >> 5)] >> (tid & 31)) & 1u;
+  int total = 0;
+  const int p = block_excl_scan<NT>(any ? 1 : 0, red, &total);
+  if (any) a.U[p] = tid;
+  if (tid == 0) *a.count = total;
+}
 
 // Top-k selection run by one extra workgroup of another kernel's launch (which leaves
 // CUs free for it), so that the selection runs beside that kernel's weight stream

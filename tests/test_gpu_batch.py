@@ -274,6 +274,45 @@ def test_batch_block(B, mode, batch_mode):
     _check_block(cfg, t, out, hs, ms, K0, V0, mode, batch_mode)
 
 
+@pytest.mark.parametrize("B,H", [(2, 3), (32, 32), (8, 33), (32, 256), (31, 256), (5, 260)])
+def test_batch_block_head_sets_and_their_union(B, H):
+    """The head sets of a batch, chosen with their union beside the neuron selection (up to 256
+    heads; 260 take launches of their own): the oracle's sets under exact ties, and the cache
+    row at pos written for a sequence's selected heads and for no other."""
+    d, dh, n, r = 64, 8, 1100, 8
+    rnd = lambda *sh: (0.1 * torch.randn(sh, device="cuda")).half()
+    attn = Bd.Attn(rnd(H * dh, d), rnd(H * dh, d), rnd(H * dh, d), rnd(H * dh, d), H)
+    mlp = Bd.MLP(rnd(n, d), rnd(n, d))
+
+    def pred(m, mul):   # scores x[b, 0] * vals, exactly
+        AT, BT = torch.zeros((r, d), device="cuda"), torch.zeros((m, r), device="cuda")
+        AT[0, 0] = 1.0
+        vals = torch.tensor([float((i * mul) % 11) - 5.0 for i in range(m)], device="cuda")
+        BT[:, 0] = vals
+        return Bd.Predictor(AT.half(), BT.half()), vals.cpu().double().numpy()
+
+    ph, vh = pred(H, 7)
+    pm, vm = pred(n, 13)
+    x = torch.randn((B, d), device="cuda")
+    x[:, 0] = torch.tensor([1.0 if b % 2 else -2.0 for b in range(B)], device="cuda")
+    for kh in sorted({1, max(1, H // 3), H}):
+        K0 = torch.randn((B, H, 5, dh), device="cuda").half()
+        kv = Bd.KVCache(K0.clone(), K0.clone(), [b % 5 for b in range(B)])
+        _, heads, idx = Bd.dv_sparse_block(attn, mlp, ph, pm, None, kv, x, kh, 40, 0.3)
+        _sync()
+        key = (x.half().float() @ attn.Wk.float().T).view(B, H, dh)
+        for b in range(B):
+            s = float(x[b, 0])
+            S = O.select_topk(s * vh, kh).tolist()
+            assert host(heads)[b].tolist() == S, (kh, b)
+            assert host(idx)[b].tolist() == O.select_topk(s * vm, 40).tolist()
+            want = K0[b].clone()
+            want[S, b % 5] = key[b, S].half()
+            assert torch.allclose(kv.K[b].float(), want.float(), rtol=2e-3, atol=2e-3), (kh, b)
+            other = [h for h in range(H) if h not in S]
+            assert torch.equal(kv.K[b, other], K0[b, other])
+
+
 def test_batch_block_deterministic():
     cfg = _cfg("small_b8")
     t = make_layer(cfg, 42, device="cuda", biases=True, ln_random=True)

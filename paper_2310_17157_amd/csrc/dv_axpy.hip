@@ -52,11 +52,14 @@ __global__ void __launch_bounds__(NW * 64) k_axpy(AxpyArgs a) {
   constexpr int E = Chunk<T>::E;
   constexpr int LR = 64 / R;                                     // lanes per row of a load
   constexpr int SW = LR * E;                                     // columns per span
+  // a lane's E sums in LDS, 4-bit rows with a gap of 16 bytes (at a stride of 128 bytes all lanes meet
+  // in the same banks)
+  constexpr int EP = E == 32 ? E + 4 : E;
   extern __shared__ float smem[];
   const int rpb = a.rows_per_batch;
   float* cf = smem;                                              // [rpb] coefficients
   int* ri = reinterpret_cast<int*>(cf + rpb);                    // [rpb] row indices
-  float* red = reinterpret_cast<float*>(ri + rpb);               // [NW][SW] wavefront sums
+  float* red = reinterpret_cast<float*>(ri + rpb);               // [NW][LR][EP] wavefront sums
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int q = R == 1 ? 0 : lane / LR, lcol = lane - q * LR;   // row of a load, lane within the row
   const int S = gridDim.y, sp = blockIdx.y;
@@ -173,14 +176,14 @@ __global__ void __launch_bounds__(NW * 64) k_axpy(AxpyArgs a) {
     for (int e = 0; e < E; ++e) acc[e] += __shfl_xor(acc[e], off);
   if (q == 0)
 #pragma unroll
-    for (int e = 0; e < E; ++e) red[wave * SW + lcol * E + e] = acc[e];
+    for (int e = 0; e < E; ++e) red[(wave * LR + lcol) * EP + e] = acc[e];
   __syncthreads();
   for (int t = tid; t < SW; t += NT) {
     const int col = blockIdx.x * SW + t;
     if (col < a.d) {
       float s = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) s += red[w * SW + t];
+      for (int w = 0; w < NW; ++w) s += red[(w * LR + t / E) * EP + t % E];
       if (S == 1) {
         if (a.resid) s += a.resid[col];
         if (a.bias) s += a.bias[col];
@@ -262,7 +265,7 @@ static hipError_t launch_axpy_t(AxpyArgs a, hipStream_t st, bool whole = false) 
   // wavefront sums.
   const int rpb = min(kAxRowsLds, max(1, (a.nrows + S - 1) / S));
   a.rows_per_batch = rpb;
-  const size_t lds = (size_t)rpb * 8 + (size_t)NW * LR * E * 4;
+  const size_t lds = (size_t)rpb * 8 + (size_t)NW * LR * (E == 32 ? E + 4 : E) * 4;
   launch_k((k_axpy<T, NW, U, HEADS, R>), dim3(spans, S), dim3(NW * 64), lds, st, a);
   if (S > 1 && a.cnt == nullptr) launch_k(k_axpy_sum, dim3((a.d / 4 + 255) / 256), dim3(256), 0, st, a, S);
   return hipGetLastError();

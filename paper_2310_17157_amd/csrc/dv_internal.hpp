@@ -65,13 +65,19 @@ __device__ __forceinline__ void unpack<_Float16>(u32x4 w, float* v) {
   for (int i = 0; i < 8; ++i) v[i] = (float)h[i];
 }
 
+// Element k (0..7) of eight 4-bit codes w, flipped once by q4_flip: code - 8 is the code with its
+// top bit inverted, sign-extended (one bit-field extract instead of an extract and an add).
+__device__ __forceinline__ uint32_t q4_flip(uint32_t w) { return w ^ 0x88888888u; }
+__device__ __forceinline__ float q4_at(uint32_t f, int k) { return (float)((int)(f << (28 - 4 * k)) >> 28); }
+
 // A 4-bit chunk as 32 floats code - 8 (the caller applies the chunk's scale).
 template <>
 __device__ __forceinline__ void unpack<q4_t>(u32x4 w, float* v) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    const uint32_t f = q4_flip(w[i]);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[8 * i + k] = (float)((int)((w[i] >> (4 * k)) & 15u) - 8);
+    for (int k = 0; k < 8; ++k) v[8 * i + k] = q4_at(f, k);
   }
 }
 
@@ -93,11 +99,17 @@ template <>
 __device__ __forceinline__ int xs_index<_Float16>(int e, int d) {
   return ((e >> 2) & 1) * (d >> 1) + ((e >> 3) << 2) + (e & 3);
 }
-// 4-bit rows: eight planes (elements 4p..4p+3 of every 32-element chunk in plane p).
+// 4-bit rows: eight planes (elements 4p..4p+3 of every 32-element chunk in plane p), each an odd
+// multiple of 32 words long, so that the staging's 16-byte stores, which go round the planes, spread
+// over all banks (planes of d / 8 words put eight lanes on the same four).
+__host__ __device__ __forceinline__ int q4_plane(int d) { return ((d / 8 + 31) / 64) * 64 + 32; }
 template <>
 __device__ __forceinline__ int xs_index<q4_t>(int e, int d) {
-  return ((e >> 2) & 7) * (d >> 3) + ((e >> 5) << 2) + (e & 3);
+  return ((e >> 2) & 7) * q4_plane(d) + ((e >> 5) << 2) + (e & 3);
 }
+// Floats of LDS the staged input takes.
+template <typename T>
+__host__ __device__ __forceinline__ int xs_floats(int d) { return kIsQ4<T> ? 8 * q4_plane(d) : d; }
 
 template <typename T>
 __device__ __forceinline__ float dot_chunk(u32x4 w, const float* xs, int d, int c, float acc);
@@ -130,15 +142,16 @@ __device__ __forceinline__ float dot_chunk<_Float16>(u32x4 w, const float* xs, i
 // Dot of a 4-bit chunk (scale sc) with its 32 staged inputs: sc * sum (code - 8) x.
 __device__ __forceinline__ float dot_chunk_q4(u32x4 w, float sc, const float* xs, int d, int c, float acc) {
   float t = 0.f;
-  const int plane = d >> 3;
+  const int plane = q4_plane(d);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const f32x4 xa = *reinterpret_cast<const f32x4*>(xs + (2 * i) * plane + 4 * c);
     const f32x4 xb = *reinterpret_cast<const f32x4*>(xs + (2 * i + 1) * plane + 4 * c);
+    const uint32_t f = q4_flip(w[i]);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) t = fmaf((float)((int)((w[i] >> (4 * k)) & 15u) - 8), xa[k], t);
+    for (int k = 0; k < 4; ++k) t = fmaf(q4_at(f, k), xa[k], t);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) t = fmaf((float)((int)((w[i] >> (4 * k + 16)) & 15u) - 8), xb[k], t);
+    for (int k = 0; k < 4; ++k) t = fmaf(q4_at(f, k + 4), xb[k], t);
   }
   return fmaf(sc, t, acc);
 }

@@ -14,7 +14,7 @@ template <typename T, int NW, int U, int KX, bool LN>
 __global__ void __launch_bounds__(NW * 64) k_fc1(Fc1Args a) {
   extern __shared__ float smem[];
   float* xs = smem;
-  float* red = smem + a.d;
+  float* red = smem + xs_floats<T>(a.d);
   float* part = red + NW;
   clear_counters(a.clear, a.clear_n);
   auto row_ptr = [&](int s) {
@@ -55,7 +55,7 @@ static hipError_t launch_fc1_t(const Fc1Args& a, hipStream_t st) {
   // as deeper queues let the XCDs that win the fabric arbitration run ahead
   constexpr int U = 2;
   const int blocks = max(1, min(a.k, device_cu_count()));
-  const size_t lds = (size_t)(a.d + NW + rowdot_flat_part(a.k, blocks, NW)) * sizeof(float);
+  const size_t lds = (size_t)(xs_floats<T>(a.d) + NW + rowdot_flat_part(a.k, blocks, NW)) * sizeof(float);
   const void* kern = a.g != nullptr ? reinterpret_cast<const void*>(k_fc1<T, NW, U, KX, true>)
                                     : reinterpret_cast<const void*>(k_fc1<T, NW, U, KX, false>);
   const hipError_t e = ensure_dyn_lds(kern, lds);

@@ -285,11 +285,10 @@ __device__ void stage_x(const float* __restrict__ x, int d, float* xs) {
   __syncthreads();
 }
 
-// Order-preserving key of a float: a > b  <=>  key(a) > key(b); -0 maps to +0.
+// Order-preserving key of a float: a > b  <=>  key(a) > key(b); -0 maps to +0 (-0 + 0 = +0).
 __device__ __forceinline__ uint32_t fkey(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u << 1) == 0u) u = 0u;
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const uint32_t u = __float_as_uint(f + 0.f);
+  return u ^ ((uint32_t)((int)u >> 31) | 0x80000000u);
 }
 
 // ------------------------------------------------------------------ host

@@ -332,7 +332,7 @@ __device__ __forceinline__ void wg_select_reg(const float* __restrict__ s, int n
   int ngt = 0, neq = 0;
   if (all_eq) {
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) ngt += __popcll(__ballot((key[j] >> sh) >= prefix));
+    for (int j = 0; j < IPT; ++j) ngt += __popcll(__ballot(key[j] >= prefix << sh));
   } else {
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
@@ -367,6 +367,7 @@ __device__ __forceinline__ void wg_select_reg(const float* __restrict__ s, int n
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)acc));
   };
   auto walk_all = [&](auto put) {   // all_eq: one predicate, one running rank
+    const uint32_t least = prefix << sh;   // (one comparison per key: the walks are issue-bound on their CU)
     int r = rg;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -374,7 +375,7 @@ __device__ __forceinline__ void wg_select_reg(const float* __restrict__ s, int n
       int bl = 0, t = 0;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        sl[e] = (key[4 * g + e] >> sh) >= prefix;
+        sl[e] = key[4 * g + e] >= least;
         const uint64_t ms = __ballot(sl[e]);
         bl = below(ms, bl);
         t += __popcll(ms);

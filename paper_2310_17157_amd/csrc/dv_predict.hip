@@ -268,8 +268,11 @@ static hipError_t launch_scores_t(const PredScoreArgs& a, hipStream_t st) {
   const int nrows = a.n0 + a.n1;
   const int hosted = a.sel_k0 > 0 ? 1 : 0;
   const size_t lds = (size_t)(((a.r0 + 3) & ~3) + ((a.r1 + 3) & ~3) + 4 * a.n0 * hosted + 4) * sizeof(float);
-  // two workgroups per CU (the head-selection workgroup included): all resident at once
-  const int blocks = max(1, min(2 * device_cu_count() - hosted, nrows));
+  // two workgroups per CU (the head-selection workgroup included): all resident at once; fewer
+  // when a wavefront's group (4 * 8 short rows, 2 long ones) per workgroup takes all rows, since
+  // short rows are little work for the wavefronts dispatched (3084 rows of 64 fp32: 6.4 -> 5.1 us)
+  const int group = nch > 32 ? 2 : (nch > 16 ? 2 * 8 : 4 * 8);
+  const int blocks = max(1, min(2 * device_cu_count() - hosted, (nrows + group - 1) / group));
   const dim3 grid(blocks + hosted, a.B);
   // hidden vectors staged behind the first loads when one float4 per thread holds them
   const bool early = max(a.r0, a.r1) <= 4 * NW * 64;
@@ -325,7 +328,7 @@ static void launch_select_reg(dim3 grid, const float* scores, int n, int mode, i
   if constexpr (IPT > 4)
     if (n <= 1024 * (IPT - 4))
       return launch_select_reg<IPT - 4, HEADS>(grid, scores, n, mode, k, thresh, idx, cap, count, idx2, heads, st);
-  launch_k(n == 1024 * IPT ? k_select<IPT, false, HEADS> : k_select<IPT, true, HEADS>, grid, dim3(1024), 0, st, scores,
+  launch_k(1024 * IPT - n <= kSelPadFew ? k_select<IPT, false, HEADS> : k_select<IPT, true, HEADS>, grid, dim3(1024), 0, st, scores,
            n, mode, k, thresh, idx, cap, count, idx2, heads);
 }
 

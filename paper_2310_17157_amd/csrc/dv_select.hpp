@@ -60,11 +60,19 @@ __device__ __forceinline__ void find_digit(const uint32_t* hist, int nb, int kre
   *above = sm[NT / kWave + 1];
 }
 
+// fkey's value by comparisons, for the streamed passes (fkey's addition there made a selection from
+// 55000 scores take 66 us instead of 49).
+__device__ __forceinline__ uint32_t fkey_stream(float f) {
+  uint32_t u = __float_as_uint(f);
+  if ((u << 1) == 0u) u = 0u;
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
 // Select over s[0..n). Writes the set to out[0..min(count, cap)) (and out2 if not
 // NULL) and the set size to *count_out (if not NULL). hist: kSelBins u32 of LDS;
 // sm: kSelSm(NT) ints of LDS. Called by the whole workgroup.
 template <int NT>
-__device__ void wg_select(const float* __restrict__ s, int n, int mode, int k, float thresh,
+__device__ __forceinline__ void wg_select(const float* __restrict__ s, int n, int mode, int k, float thresh,
                           int32_t* __restrict__ out, int cap, int32_t* __restrict__ count_out,
                           int32_t* __restrict__ out2, uint32_t* hist, int* sm) {
   const int tid = threadIdx.x;
@@ -97,7 +105,7 @@ __device__ void wg_select(const float* __restrict__ s, int n, int mode, int k, f
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const uint32_t key = fkey(v[u]);
+          const uint32_t key = fkey_stream(v[u]);
           if (b + u * NT + tid < n && (pbits == 0 || shr32(key, hi) == prefix))
             atomicAdd(&hist[(key >> lo) & (uint32_t)(nb - 1)], 1u);
         }
@@ -139,7 +147,7 @@ __device__ void wg_select(const float* __restrict__ s, int n, int mode, int k, f
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const int i = b + u * 64 + lane;
-      const uint32_t key = shr32(fkey(v[u]), sh);
+      const uint32_t key = shr32(fkey_stream(v[u]), sh);
       const bool in = i < w1;
       cgt += __popcll(__ballot(in && (all || key > prefix)));
       ceq += __popcll(__ballot(in && !all && key == prefix));
@@ -171,7 +179,7 @@ __device__ void wg_select(const float* __restrict__ s, int n, int mode, int k, f
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const int i = b + u * 64 + lane;
-      const uint32_t key = shr32(fkey(v[u]), sh);
+      const uint32_t key = shr32(fkey_stream(v[u]), sh);
       const bool in = i < w1;
       const bool gt = in && (all || key > prefix);
       const bool eq = in && !all && key == prefix;
@@ -204,10 +212,10 @@ __device__ void wg_select(const float* __restrict__ s, int n, int mode, int k, f
 // Slots past n hold key 0, which no real score produces (every finite or infinite
 // float maps above 2^22), so they never match a selected prefix and need no separate
 // validity test (k >= n, where every score is taken, writes 0..n-1 directly). They are
-// kept out of the first histogram (PAD): counted, they all fall in one bin, and the LDS
+// kept out of the first histogram where they are many (PAD): counted, they all fall in one bin, and the LDS
 // atomics of one address run a lane at a time (3072 scores in 48 slots per thread: 55 us
-// for the launch that hosts the selection, 16384 scores: 38.6 us). Without padding
-// (n = NT * IPT) the predicate is left out, 1.6 us less at 49152 scores. The selection
+// for the launch that hosts the selection, 16384 scores: 38.6 us). With little padding
+// the predicate is left out, 1.6 us less at 49152 scores. The selection
 // boundary is re-read from LDS,
 // wavefront-uniform, before the write walk, so the compiler recomputes the per-key
 // predicates instead of keeping them live across the scans.
@@ -486,11 +494,15 @@ __device__ void wg_select_small(const float* __restrict__ s, int n, int mode, in
   __syncthreads();
 }
 
-// Most slots per thread of wg_select_reg (49152 scores). A call takes the fewest that hold
-// its scores (as a launch of its own any multiple of 4, hosted 4, 16 or 48), so that every
+// Most slots per thread of wg_select_reg (61440 scores; 55000 scores streamed from memory took 49 us
+// for the predictor's call, in registers 30). A call takes the fewest that hold
+// its scores (as a launch of its own any multiple of 4, hosted 4, 16, 48 or 60), so that every
 // wavefront has a share of a short vector: with 48 slots the first wavefront alone would
 // hold 3072 scores and walk them serially.
-constexpr int kSelIPT = 48;
+constexpr int kSelIPT = 60;
+// Padding slots up to which their count in one bin (about 1 ns each) costs less than keeping
+// them out.
+constexpr int kSelPadFew = 1024;
 
 // The head sets of a batch by one workgroup: for each of B rows of H scores the k highest (ties
 // to the lower index, k >= H: every head) by rank counting, and from the sets their union, its
@@ -540,7 +552,7 @@ __device__ __forceinline__ void wg_head_sets(const HeadSets& a, uint32_t* keys, 
 // callee-saved registers besides its own spills, which raised the host kernel's
 // private segment to 336 bytes per lane and its duration by 1.5-2 us on the
 // 3 x 4096-row QKV launch (inlined: 120 bytes).
-// Up to 48 * NT scores are selected from registers, larger score vectors stream from
+// Up to kSelIPT * NT scores are selected from registers, larger score vectors stream from
 // memory. smem: kSelBins u32 plus kSelSm(NT) ints of LDS.
 
 template <int NT>
@@ -552,6 +564,8 @@ __device__ __forceinline__ void hosted_select(const float* scores, int n, int k,
     wg_select_reg<NT, 4, false, true>(scores, n, DV_SELECT_TOPK, k, 0.f, idx, k, nullptr, idx_out, hist, sm);
   else if (n <= NT * 16)
     wg_select_reg<NT, 16, false, true>(scores, n, DV_SELECT_TOPK, k, 0.f, idx, k, nullptr, idx_out, hist, sm);
+  else if (n <= NT * 48)
+    wg_select_reg<NT, 48, false, true>(scores, n, DV_SELECT_TOPK, k, 0.f, idx, k, nullptr, idx_out, hist, sm);
   else if (n <= NT * kSelIPT)
     wg_select_reg<NT, kSelIPT, false, true>(scores, n, DV_SELECT_TOPK, k, 0.f, idx, k, nullptr, idx_out, hist, sm);
   else

@@ -177,10 +177,10 @@ def test_select_paths_agree_with_oracle(n):
     assert host(idx)[0][:cap].tolist() == full[:cap]
 
 
-@pytest.mark.parametrize("n", [1026, 4095, 4096, 4097, 16383, 16384, 16388, 49152])
+@pytest.mark.parametrize("n", [1026, 3000, 3072, 4095, 4096, 4097, 16383, 16384, 16388, 49152, 49153, 60416, 61439, 61440, 61441])
 def test_select_slots_per_thread(n):
-    """The register select keeps 4, 16 or 48 scores per thread by the vector's length (to
-    4096, 16384 and 49152 scores): at and beside those lengths, for two rows (the second
+    """The register select keeps 4 to 60 scores per thread by the vector's length (to 61440
+    scores), its padding slots counted up to 1024 of them: at and beside those lengths, for two rows (the second
     one misaligned when n is not a multiple of 4) of few distinct values, so that the
     boundary ties, and a set of -inf, +inf, zeros of both signs and NaN-free extremes."""
     d, r = 64, 8
@@ -513,6 +513,14 @@ def test_sparse_block_at_the_rank_limit():
     cfg = get_config("small_f16").with_(name="r16000", d=256, N=512, H=4, dh=64, L=40, r=16000,
                                         k_mlp=100, k_heads=2)
     _block(cfg, 46, Bd.DV_LOOKAHEAD)
+
+
+@pytest.mark.parametrize("N", [4096, 4104, 16392, 49160, 61440])
+def test_sparse_block_hosted_selection_slots(N):
+    """The neuron top-k hosted in the QKV launch, at the edges of its 4, 16, 48 and 60 slots
+    per thread."""
+    cfg = get_config("small_f16").with_(name=f"n{N}", d=256, N=N, H=4, dh=64, L=40, r=64, k_mlp=N // 20, k_heads=2)
+    _block(cfg, 48, Bd.DV_LOOKAHEAD)
 
 
 def test_sparse_block_neuron_selection_streams_past_49152():

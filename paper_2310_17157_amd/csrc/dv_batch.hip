@@ -290,11 +290,16 @@ hipError_t launch_cast_union(const float* x, int B, int NB, int d, int Kpad, con
 // (lr, lg) takes row lr, chunk 4h + lg for k-step h of the block. A tile's reads go on for up to
 // four blocks (512 bytes of a row) before the next tile's.
 //
-// XF32: the inputs stay fp32 to 24 bits. A superblock (two blocks) of a token is scaled by a
-// power of two to below 2^14 and split into three fp16 terms (11 bits each), whose products
-// with the fp16 weights are exact; the fp32 sums over one superblock, of the first and of
-// the smaller terms apart, are added in fp64. Two terms would lose a bit and a half against
-// fp32, one fp32 sum over all superblocks another.
+// XF32: the inputs stay fp32. A superblock of a token is scaled by a power of two to below
+// 2^14 and split into three fp16 terms of 11 bits, the second held times 2^11 and the third times 2^22,
+// so that an element down to 2^-23 after the scaling (2^-37 of the superblock's largest) is their sum
+// exactly. Their products with the fp16 weights are exact; the fp32 sums over one
+// superblock, one per term, are added in fp64. Two terms would lose a bit and a half against
+// fp32, one fp32 sum over all superblocks another, and three terms under one scale would lose elements
+// below 2^-14 of the largest one (at 10^8 under an element that meets zero weights, 2.6e-4 of the result,
+// against 1.2e-7 here and 1.6e-7 in fp32 FMAs). Where a token still has smaller elements but zero, its
+// rows are computed again in fp64 from the inputs as they are (rows_dot), and so are sums that are
+// not finite: a term is zero where the input is not, and an infinite weight makes that NaN.
 template <int MODE>
 __device__ __forceinline__ int rows_count(const RowsSrc& s) {
   if constexpr (MODE == kRowsIdentity) {
@@ -339,6 +344,24 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// XF32: elements [k0, k1) of weight row id times token b, in fp64.
+template <int MODE>
+__device__ __forceinline__ float rows_dot(const RowsArgs& a, const RowsSrc& s, int id, int b, int k0, int k1) {
+  const char* w = rows_addr<MODE>(s, id);
+  const float* x = static_cast<const float*>(s.X) + (size_t)b * s.d;
+  double v = 0.;
+#pragma unroll 1
+  for (int k = k0; k < k1; k += 8) {
+    const f16x8 h = __builtin_bit_cast(f16x8, ld_plain(w + (size_t)k * 2));
+    for (int e = 0; e < 8; ++e) {
+      float xe = x[k + e];
+      for (int p = 1; p < a.XP; ++p) xe += x[(size_t)p * a.B * s.d + k + e];
+      v = fma((double)h[e], (double)xe, v);
+    }
+  }
+  return (float)v;
+}
+
 // Epilogue of one value: row r (of n), token b.
 template <int EPI, int NB, typename KT>
 __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const RowsSrc& s, int r, int n, int b, int sp, float v) {
@@ -373,10 +396,10 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const RowsSrc& 
 
 constexpr int kRowsNW = 8;
 // Tiles per round of the sums through LDS.
-template <int NB, bool XF32, int MT> constexpr int kRowsRT = MT < 5 ? MT : (XF32 && NB == 32 ? 2 : 5);
+template <int MT> constexpr int kRowsRT = MT < 5 ? MT : 5;
 template <int NB, bool XF32, int MT>
 constexpr size_t rows_lds() {
-  return (size_t)kRowsNW * (16 * 64 * 2 + kRowsRT<NB, XF32, MT> * 16 * (NB + 1) * (XF32 ? 8 : 4));
+  return (size_t)kRowsNW * (16 * 64 * 2 + kRowsRT<MT> * 16 * (NB + 1) * (XF32 ? 8 : 4));
 }
 
 // MT: tiles a wavefront accumulates in registers at a time; SB: blocks of a superblock (a power
@@ -384,7 +407,7 @@ constexpr size_t rows_lds() {
 template <int NB, int MODE, int EPI, bool XF32, typename KT, int MT, int SB, int TB>
 __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
   constexpr int NW = kRowsNW, NT = NW * 64, NBT = NB / 16;
-  constexpr int RT = kRowsRT<NB, XF32, MT>;
+  constexpr int RT = kRowsRT<MT>;
   using Sum = std::conditional_t<XF32, double, float>;
   extern __shared__ __attribute__((aligned(16))) _Float16 rsm[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -397,8 +420,10 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
   const bool sec = TWO && (int)blockIdx.x >= a.G0;
   const RowsSrc& s = TWO ? a.src[sec ? 1 : 0] : a.src[0];
   const int S = XF32 ? a.S : 1, sp = XF32 ? (int)blockIdx.x % S : 0;   // split of the contraction
-  const int wg = TWO ? (int)blockIdx.x - (sec ? a.G0 : 0) : (int)blockIdx.x / S;
-  const int G = TWO ? (sec ? (int)gridDim.x - a.G0 : a.G0) : (int)gridDim.x / S;
+  // XF32: workgroups [0, G) take tokens [0, NB), the next G (S == 1) the tokens from NB
+  const int b0 = XF32 && (int)blockIdx.x >= a.G0 ? NB : 0;
+  const int wg = TWO ? (int)blockIdx.x - (sec ? a.G0 : 0) : (XF32 ? (int)blockIdx.x % a.G0 : (int)blockIdx.x) / S;
+  const int G = TWO ? (sec ? (int)gridDim.x - a.G0 : a.G0) : (XF32 ? a.G0 : (int)gridDim.x) / S;
   if constexpr (EPI == kEpiQkv) {
     // the attention's coefficient matrix, before it writes its part
     if (a.zero != nullptr)
@@ -431,6 +456,7 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
       for (int j = 0; j < NBT; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[q][j][i] = 0;
+    bool wide[NBT] = {};                         // XF32: elements the split does not hold exactly
 
     auto super = [&](auto blocks, int kb) {
       constexpr int NBLK = decltype(blocks)::value;
@@ -458,7 +484,7 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
           const int k = (2 * kb + ks) * 32 + 8 * lg;
 #pragma unroll
           for (int j = 0; j < NBT; ++j) {
-            const float* xp = static_cast<const float*>(s.X) + (size_t)min(lr + 16 * j, a.B - 1) * s.d + min(k, s.d - 8);
+            const float* xp = static_cast<const float*>(s.X) + (size_t)min(b0 + lr + 16 * j, a.B - 1) * s.d + min(k, s.d - 8);
             xv[ks][j][0] = *reinterpret_cast<const f32x4*>(xp);
             xv[ks][j][1] = *reinterpret_cast<const f32x4*>(xp + 4);
             for (int p = 1; p < a.XP; ++p) {     // inputs given as parts (few): their sum
@@ -473,6 +499,7 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
 #pragma unroll
         for (int j = 0; j < NBT; ++j) {
           float m = 0.f;
+          uint32_t least = ~0u;                        // bits of the smallest magnitude but 0, less one
 #pragma unroll
           for (int ks = 0; ks < 2 * NBLK; ++ks) {
             const bool in = (2 * kb + ks) * 32 + 8 * lg < s.d;
@@ -481,6 +508,7 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
               const float v = in ? xv[ks][j][e >> 2][e & 3] : 0.f;
               xv[ks][j][e >> 2][e & 3] = v;
               m = fmaxf(m, fabsf(v));
+              least = min(least, (__float_as_uint(v) & 0x7fffffffu) - 1u);
             }
           }
           m = fmaxf(m, __shfl_xor(m, 16, kWave));
@@ -489,19 +517,22 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
           const int e2 = min(max(140 - (int)((__float_as_uint(m) >> 23) & 255u), -126), 126);
           const float sc = __uint_as_float((uint32_t)(e2 + 127) << 23);
           inv[j] = __uint_as_float((uint32_t)(127 - e2) << 23);
+          wide[j] |= least + 1u < __float_as_uint(0x1p-23f * inv[j]) && least != ~0u;
 #pragma unroll
-          for (int ks = 0; ks < 2 * NBLK; ++ks)
+          for (int ks = 0; ks < 2 * NBLK; ++ks) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
               const float v = xv[ks][j][e >> 2][e & 3] * sc;
               const _Float16 hi = (_Float16)v;
-              float rest = v - (float)hi;
+              float rest = (v - (float)hi) * 0x1p11f;
               rest = fabsf(v) < 32768.f ? rest : 0.f;          // (infinities and NaN: the first term alone)
               const _Float16 mid = (_Float16)rest;
-              bf[ks][j][0][e] = (_Float16)(rest - (float)mid);
+              bf[ks][j][0][e] = (_Float16)((rest - (float)mid) * 0x1p11f);
               bf[ks][j][TERMS - 2][e] = mid;
               bf[ks][j][TERMS - 1][e] = hi;
             }
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
       } else {
 #pragma unroll
@@ -527,10 +558,10 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
 #pragma unroll
         for (int tt = 0; tt < N; ++tt) {
           const int q = q0 + tt;
-          f32x4 t[NBT], tl[NBT];                               // (XF32: the first terms; the small ones)
+          f32x4 t[NBT], tm[NBT], tl[NBT];                      // (XF32: a sum per term)
 #pragma unroll
           for (int j = 0; j < NBT; ++j) {
-            tl[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            tm[j] = tl[j] = f32x4{0.f, 0.f, 0.f, 0.f};
             if constexpr (XF32) t[j] = tl[j];
             else t[j] = f32x4{acc[q][j][0], acc[q][j][1], acc[q][j][2], acc[q][j][3]};
           }
@@ -551,7 +582,7 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
               for (int j = 0; j < NBT; ++j) {
                 if constexpr (XF32) {
                   tl[j] = mfma16x16x32(av, bf[2 * blk + h][j][0], tl[j]);
-                  tl[j] = mfma16x16x32(av, bf[2 * blk + h][j][1], tl[j]);
+                  tm[j] = mfma16x16x32(av, bf[2 * blk + h][j][1], tm[j]);
                 }
                 t[j] = mfma16x16x32(av, bf[2 * blk + h][j][TERMS - 1], t[j]);
               }
@@ -562,7 +593,8 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
           for (int j = 0; j < NBT; ++j)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              if constexpr (XF32) acc[q][j][i] += ((double)t[j][i] + (double)tl[j][i]) * (double)inv[j];
+              if constexpr (XF32)
+                acc[q][j][i] += ((double)t[j][i] + (double)fmaf(tl[j][i], 0x1p-11f, tm[j][i]) * 0x1p-11) * (double)inv[j];
               else acc[q][j][i] = t[j][i];
             }
         }
@@ -571,7 +603,7 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
       for (int q0 = 0; q0 < MT; q0 += TB) {
         if (q0 + TB <= T && q0 + TB <= MT) {
           tiles(std::integral_constant<int, TB>{}, q0);
-        } else {
+        } else if constexpr (TB > 1) {
 #pragma unroll
           for (int q = q0; q < q0 + TB && q < MT; ++q)
             if (q < T) tiles(std::integral_constant<int, 1>{}, q);
@@ -592,6 +624,16 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
       }
     for (; kb < kb1; ++kb) super(std::integral_constant<int, 1>{}, kb);
 
+    if constexpr (XF32)
+#pragma unroll
+      for (int j = 0; j < NBT; ++j) {
+        int w = wide[j];
+        w |= __shfl_xor(w, 16, kWave);
+        w |= __shfl_xor(w, 32, kWave);
+        if (w)
+#pragma unroll
+          for (int q = 0; q < MT; ++q) acc[q][j][0] = acc[q][j][1] = acc[q][j][2] = acc[q][j][3] = NAN;
+      }
     // ---- the wavefronts' sums added in order, RT tiles at a time (lane: rows 4 lg + i,
     // tokens lr + 16 j of a tile)
 #pragma unroll
@@ -607,12 +649,18 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
             red[((wave * RT + (q - t0)) * 16 + 4 * lg + i) * (NB + 1) + lr + 16 * j] = acc[q][j][i];
       __syncthreads();
       for (int e = tid; e < min(RT, T - t0) * 16 * NB; e += NT) {
-        const int rr = e & 15, b = (e >> 4) % NB, q = (e >> 4) / NB;
+        const int rr = e & 15, bl = (e >> 4) % NB, q = (e >> 4) / NB, b = b0 + bl;
         const int r = c0 + 16 * (t0 + q) + rr;
         if (r >= r1) continue;
         Sum v = 0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) v += red[((w * RT + q) * 16 + rr) * (NB + 1) + b];
+        for (int w = 0; w < NW; ++w) v += red[((w * RT + q) * 16 + rr) * (NB + 1) + bl];
+        if constexpr (XF32)
+          if (b < a.B && !(fabs(v) < INFINITY)) {
+            int ro = r, bo = b;                        // (opaque: nothing of it is computed ahead)
+            asm volatile("" : "+v"(ro), "+v"(bo));
+            v = rows_dot<MODE>(a, s, rows_id<MODE>(s, ro, n), bo, sb0 * 64, min((sb0 + sbn) * 64, s.d));
+          }
         rows_epilogue<EPI, NB, KT>(a, s, r, n, b, sp, (float)v);
       }
     }
@@ -657,12 +705,18 @@ static hipError_t launch_rows_t(RowsArgs a, hipStream_t st) {
   const double w0 = (double)a.src[0].nrows * a.src[0].d, w1 = (double)a.src[1].nrows * a.src[1].d;
   a.G0 = a.src[1].W0 == nullptr ? G : min(max((int)(G * w0 / (w0 + w1) + 0.5), 1), G - 1);
   if constexpr (XF32) {
-    // (tiles in flight at the OPT-66B predictor's scores, 16 inputs: 1, 2, 3, 5: 24.1, 21.4, 21.7,
-    // 31.5 us)
-    if (a.S > 1)
-      return launch_rows_v<NB, MODE, EPI, XF32, KT, 1, NB == 16 ? 4 : 2, 1>(a, (a.src[0].nrows + 15) / 16 * a.S, st);
+    if (a.S > 1) {
+      a.G0 = (a.src[0].nrows + 15) / 16 * a.S;
+      return launch_rows_v<NB, MODE, EPI, XF32, KT, 1, NB == 16 ? 4 : 2, 1>(a, a.G0, st);
+    }
+    // Nine tiles with two tiles' loads in flight fill the registers (ten tiles, or loads of one or three,
+    // spill). 17 to 32 inputs are two workgroups of 16 for each share of the rows, the second reading
+    // them from L2: with all of them in one workgroup the fp64 sums spill at two tiles already
+    // (32 inputs at the OPT-6.7B, 66B, 175B predictors, the whole call: 56, 117, 142 us; this way 37, 68, 87).
     a.S = 1;
-    return launch_rows_v<NB, MODE, EPI, XF32, KT, NB == 16 ? 10 : 4, 2, NB == 16 ? 2 : 1>(a, G, st);
+    const int parts = (a.B + 15) / 16;
+    a.G0 = G / parts;
+    return launch_rows_v<16, MODE, EPI, XF32, KT, 9, 2, 2>(a, a.G0 * parts, st);
   } else {
     // few rows (to one tile per workgroup): one tile, longer superblocks. Otherwise two tiles'
     // loads in flight with 16 tokens (four: QKV of the OPT-6.7B heads 29.5 against 24.4 us), one

@@ -558,7 +558,7 @@ struct RowsSrc {
 enum { kEpiFc1 = 0, kEpiQkv = 1, kEpiCoef = 2, kEpiOut = 3 };
 struct RowsArgs {
   RowsSrc src[2];                    // src[1].W0 == NULL: one source
-  int G0;                            // set by the launcher
+  int G0;                            // set by the launcher: workgroups of the first source (fp32 inputs: of the first tokens)
   int B;
   int S, XP;                         // fp32 inputs: splits of the contraction; parts [XP][B][d] X is the sum of
   // kEpiFc1: C(r, b) = fp16(sigma(v + b1[list[r]])), 0 where bit b of mask[r] is clear, and for

@@ -108,6 +108,57 @@ def test_predict_batch_scores_to_fp32(B, d, r, n):
             assert err < 3e-7, (size, b, err)
 
 
+@pytest.mark.parametrize("ratio", [1e3, 1e5, 1e8, 1e12, 1e30])
+@pytest.mark.parametrize("B,d,r,n", [(2, 72, 24, 40), (16, 1288, 200, 5000), (20, 392, 1000, 300), (5, 12288, 1016, 131)])
+def test_predict_batch_small_inputs_beside_large_ones(B, d, r, n, ratio):
+    """Inputs far below the largest of their neighbours keep fp32's precision: the large ones (every 64th input
+    and every 16th hidden value, ratio times the others) meet zero weights, so that the scores are those of
+    the small ones alone. The same bound as above."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B * 1000 + d)
+    rnd = lambda *sh: torch.randn(sh, generator=g, device="cuda")
+    AT, BT = (0.02 * rnd(r, d)).half(), (0.02 * rnd(n, r)).half()
+    x = rnd(B, d)
+    x[:, 5::64] *= ratio
+    AT[:, 5::64] = 0                     # but one hidden value, which no score takes
+    AT[3::16] = 0
+    AT[3::16, 5] = 1.0
+    BT[:, 3::16] = 0
+    pred = Bd.Predictor(AT, BT)
+    sc = torch.empty((B, n), dtype=torch.float32, device="cuda")
+    Bd.dv_predict_mlp(pred, x, 1, scores=sc)
+    ref = (x.double() @ AT.double().T) @ BT.double().T
+    _sync()
+    for b in range(B):
+        err = float((sc[b].double() - ref[b]).norm() / ref[b].norm())
+        assert err < 3e-7, (b, err)
+
+
+def test_predict_batch_infinite_weights_as_one_input():
+    """A score or a hidden value over an infinite factor is the infinity (or NaN) that the inputs give one at a
+    time, also where an input fills less than 24 bits."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    AT = torch.randn((40, 392), generator=g, device="cuda").half()
+    BT = torch.randn((70, 40), generator=g, device="cuda").half()
+    x = torch.randn((18, 392), generator=g, device="cuda")
+    x[1, 7], x[2, 7], x[3, 7] = 0.25, -2.0, 0.0
+    for in_first in (True, False):
+        A, Bm = AT.clone(), BT.clone()
+        (A if in_first else Bm)[9, 7] = float("inf")
+        pred = Bd.Predictor(A, Bm)
+        sc = torch.empty((18, 70), dtype=torch.float32, device="cuda")
+        one = torch.empty_like(sc)
+        Bd.dv_predict_mlp(pred, x, 1, scores=sc)
+        for b in range(18):
+            Bd.dv_predict_mlp(pred, x[b:b + 1], 1, scores=one[b:b + 1])
+        _sync()
+        assert (~torch.isfinite(one)).any()
+        assert torch.equal(torch.isnan(sc), torch.isnan(one))
+        far = torch.isinf(one)
+        assert torch.equal(far, torch.isinf(sc)) and torch.equal(sc[far], one[far])
+
+
 def test_predict_batch_infinities_stay_in_their_row():
     """An infinite or NaN input makes its own row's scores non-finite and no other's."""
     g = torch.Generator(device="cuda")

@@ -209,16 +209,22 @@ __device__ __forceinline__ void wg_select(const float* __restrict__ s, int n, in
 // ranks come from ballot popcounts per group plus the per-wavefront totals; no
 // further memory round trips. Requires n <= NT * IPT.
 //
-// Slots past n hold key 0, which no real score produces (every finite or infinite
-// float maps above 2^22), so they never match a selected prefix and need no separate
-// validity test (k >= n, where every score is taken, writes 0..n-1 directly). They are
+// Slots past n hold key 0, below every finite or infinite score's, so they never match a selected
+// prefix and need no separate validity test (k >= n, where every score is taken, writes 0..n-1 directly). They are
 // kept out of the first histogram where they are many (PAD): counted, they all fall in one bin, and the LDS
 // atomics of one address run a lane at a time (3072 scores in 48 slots per thread: 55 us
 // for the launch that hosts the selection, 16384 scores: 38.6 us). With little padding
-// the predicate is left out, 1.6 us less at 49152 scores. The selection
+// the predicate is left out, 1.6 us less at 49152 scores. The negative NaN of the largest payloads
+// map to that key or share its 13-bit prefix: kept out, the padding must not be confused with them, so
+// their keys are raised past that prefix (0.4 us at 53248 scores); counted, it comes after them in index order. The selection
 // boundary is re-read from LDS,
 // wavefront-uniform, before the write walk, so the compiler recomputes the per-key
 // predicates instead of keeping them live across the scans.
+// Every finite or infinite float maps above kLeastKey; with RAISE the negative NaN that map below it are raised to it.
+constexpr uint32_t kLeastKey = 1u << 19;
+template <bool RAISE>
+__device__ __forceinline__ uint32_t slot_key(float f) { return RAISE ? max(fkey(f), kLeastKey) : fkey(f); }
+
 template <int NT, int IPT, bool OVERLAP, bool PAD>
 __device__ __forceinline__ void wg_select_reg(const float* __restrict__ s, int n, int mode, int k, float thresh,
                               int32_t* __restrict__ out, int cap, int32_t* __restrict__ count_out,
@@ -250,7 +256,7 @@ __device__ __forceinline__ void wg_select_reg(const float* __restrict__ s, int n
       const int i = wbase + 256 * g;
       const f32x4 v = *reinterpret_cast<const f32x4*>(s + min(i, n - 4));
 #pragma unroll
-      for (int e = 0; e < 4; ++e) key[4 * g + e] = i < n ? fkey(v[e]) : 0u;
+      for (int e = 0; e < 4; ++e) key[4 * g + e] = i < n ? slot_key<PAD>(v[e]) : 0u;
     }
     if (radix) {
 #pragma unroll
@@ -263,13 +269,13 @@ __device__ __forceinline__ void wg_select_reg(const float* __restrict__ s, int n
       const int i = wbase + 256 * g;
       if (vec && i + 3 < n) {
         const f32x4 v = *reinterpret_cast<const f32x4*>(s + i);
-        key[4 * g] = fkey(v[0]);
-        key[4 * g + 1] = fkey(v[1]);
-        key[4 * g + 2] = fkey(v[2]);
-        key[4 * g + 3] = fkey(v[3]);
+        key[4 * g] = slot_key<PAD>(v[0]);
+        key[4 * g + 1] = slot_key<PAD>(v[1]);
+        key[4 * g + 2] = slot_key<PAD>(v[2]);
+        key[4 * g + 3] = slot_key<PAD>(v[3]);
       } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) key[4 * g + e] = i + e < n ? fkey(s[i + e]) : 0u;
+        for (int e = 0; e < 4; ++e) key[4 * g + e] = i + e < n ? slot_key<PAD>(s[i + e]) : 0u;
       }
     }
   }
@@ -277,7 +283,7 @@ __device__ __forceinline__ void wg_select_reg(const float* __restrict__ s, int n
   int pbits = 0;
   int eq_take = INT_MAX;
   if (mode == DV_SELECT_THRESHOLD) {
-    prefix = fkey(thresh);
+    prefix = slot_key<true>(thresh);
     pbits = 32;
   } else if (k >= n) {
     // every score, in index order (the padding slots' keys must not be counted)

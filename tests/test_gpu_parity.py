@@ -259,6 +259,46 @@ def test_select_slots_per_thread(n):
         assert int(cnt[b]) == len(full) and host(idx)[b][: len(full)].tolist() == full
 
 
+@pytest.mark.parametrize("n", [96, 1026, 3000, 3072, 16384, 20000, 61440, 61441])
+def test_select_nan_scores_stay_in_range(n):
+    """With NaN among the scores the set is unspecified, but still k ascending indices of [0, n): NaN of either
+    sign, with a payload of all ones too (the lowest key there is), in place of most scores."""
+    d, r = 64, 8
+    AT = torch.zeros((r, d), dtype=torch.float32, device="cuda")
+    AT[0, 0] = 1.0
+    x = torch.zeros((2, d), dtype=torch.float32, device="cuda")
+    x[:, 0] = 1.0
+    for bits in (-1, -(1 << 13), -(1 << 22), 0x7FFFFFFF, 0x7FC00000):
+        BT = torch.zeros((n, r), dtype=torch.float32, device="cuda")
+        BT[:, 0] = torch.arange(n, device="cuda") % 97
+        BT.view(torch.int32)[7:, 0] = bits
+        pred = Bd.Predictor(AT, BT)
+        for k in (1, 7, 8, n // 2, n - 1, n):
+            idx, cnt = Bd.dv_predict_mlp(pred, x, k)
+            _sync()
+            for b in range(2):
+                s = host(idx)[b]
+                assert int(cnt[b]) == k and s[0] >= 0 and s[-1] < n and (np.diff(s) > 0).all(), (n, bits, k, b)
+        for thresh in (50.0, float("nan"), -float("inf")):
+            idx = torch.full((2, n), -1, dtype=torch.int32, device="cuda")
+            idx, cnt = Bd.dv_predict_mlp(pred, x, mode=Bd.DV_SELECT_THRESHOLD, thresh=thresh, idx=idx, cap_idx=n)
+            _sync()
+            for b in range(2):
+                s = host(idx)[b][: int(cnt[b])]
+                assert int(cnt[b]) <= n and (len(s) == 0 or (s[0] >= 0 and s[-1] < n and (np.diff(s) > 0).all()))
+
+
+def test_block_nan_predictor_scores_stay_in_range():
+    """The layer's selection, which another launch hosts: NaN scores of the lowest keys leave a set of k indices."""
+    cfg, t = layer("small_f16", 15)
+    t["BT_m"].view(torch.int16)[cfg.k_mlp // 2:] = -1
+    attn, mlp, ph, pm, kv, ln = layer_objects(t, cfg.H)
+    _, _, idx = Bd.dv_sparse_block(attn, mlp, ph, pm, ln, kv, t["x"], cfg.k_heads, cfg.k_mlp, cfg.dh ** -0.5)
+    _sync()
+    s = host(idx)[0]
+    assert len(s) == cfg.k_mlp and s[0] >= 0 and s[-1] < cfg.N and (np.diff(s) > 0).all()
+
+
 def test_select_register_path_large_sets():
     """Register-resident selection (n <= 49152) of sets too large to stage in LDS
     (more than 8128 members) is written straight to memory: top-k with and without a

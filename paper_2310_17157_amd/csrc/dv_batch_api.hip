@@ -277,18 +277,21 @@ static dv_status bpredict(const _Float16* x16, int d, int B, const dv_predictor*
   return DV_OK;
 }
 
-// Scores of one predictor for up to kMaxBatch fp32 inputs, the products to fp32's precision.
-dv_status batch_scores(const dv_predictor* p, const float* x, int B, int splits, float* hid, float* scores,
-                       hipStream_t hs) {
-  const int NB = batch_nb(B);
+// The layers of one predictor for up to kMaxBatch fp32 inputs, the products to fp32's precision.
+dv_status batch_hidden(const dv_predictor* p, const float* x, int B, int splits, float* hid, hipStream_t hs) {
   RowsArgs r{};
   RowsSrc& rs = r.src[0];
   rs.d = p->d; rs.X = x; rs.W0 = p->AT; rs.n0 = p->r; rs.nrows = p->r; rs.out = hid;
   r.B = B; r.S = splits; r.XP = 1;
-  DV_LAUNCH("pred_hidden", hs, launch_rows(NB, kEpiOut, DV_F32, true, r, hs));
+  DV_LAUNCH("pred_hidden", hs, launch_rows(batch_nb(B), kEpiOut, DV_F32, true, r, hs));
+  return DV_OK;
+}
+dv_status batch_scores(const dv_predictor* p, const float* hid, int B, int splits, float* scores, hipStream_t hs) {
+  RowsArgs r{};
+  RowsSrc& rs = r.src[0];
   rs.d = p->r; rs.X = hid; rs.W0 = p->BT; rs.n0 = p->n_out; rs.nrows = p->n_out; rs.out = scores;
-  r.S = 1; r.XP = splits;
-  DV_LAUNCH("pred_scores", hs, launch_rows(NB, kEpiOut, DV_F32, true, r, hs));
+  r.B = B; r.S = 1; r.XP = splits;
+  DV_LAUNCH("pred_scores", hs, launch_rows(batch_nb(B), kEpiOut, DV_F32, true, r, hs));
   return DV_OK;
 }
 

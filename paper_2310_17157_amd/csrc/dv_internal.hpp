@@ -620,9 +620,9 @@ hipError_t launch_attn_finish(int NB, const AttnFinishArgs& a, hipStream_t st);
 // Host side of the batched path (dv_batch_api.hip); arguments already validated.
 int batch_nb(int B);
 int batch_max_rank(int B);
-// Scores of one fp16 predictor for up to kMaxBatch fp32 inputs (hid: [splits][B][r]).
-dv_status batch_scores(const dv_predictor* p, const float* x, int B, int splits, float* hid, float* scores,
-                       hipStream_t hs);
+// The layers of one fp16 predictor for up to kMaxBatch fp32 inputs (hid: [splits][B][r], their sum the layer).
+dv_status batch_hidden(const dv_predictor* p, const float* x, int B, int splits, float* hid, hipStream_t hs);
+dv_status batch_scores(const dv_predictor* p, const float* hid, int B, int splits, float* scores, hipStream_t hs);
 size_t batch_mlp_ws(const dv_mlp* m, int B, int n_idx, int per_seq);
 size_t batch_attn_ws(const dv_attn* a, int B, int n_heads);
 size_t batch_block_ws(const dv_attn* a, const dv_mlp* m, const dv_predictor* pa, const dv_predictor* pm, int B,

@@ -443,23 +443,45 @@ static dv_status predict_impl(const dv_predictor* p, const float* x, int32_t B, 
   }
   hipStream_t hs = static_cast<hipStream_t>(stream);
 
+  // The two layers of inputs [b, b + nb), the weights read once per input.
+  auto hidden_each = [&](int b, int nb) -> dv_status {
+    PredHidArgs ha{};
+    ha.d = p->d; ha.B = nb; ha.x = x + (size_t)b * p->d; ha.g = nullptr; ha.be = nullptr; ha.eps = 0.f;
+    ha.AT0 = p->AT; ha.r0 = p->r; ha.hid0 = hid; ha.AT1 = nullptr; ha.r1 = 0; ha.hid1 = nullptr;
+    DV_LAUNCH("pred_hidden", hs, launch_pred_hidden(p->wtype, ha, hs));
+    return DV_OK;
+  };
+  auto scores_each = [&](int b, int nb) -> dv_status {
+    PredScoreArgs sa{};
+    sa.r0 = p->r; sa.n0 = p->n_out; sa.BT0 = p->BT; sa.hid0 = hid; sa.s0 = s + (size_t)b * p->n_out;
+    sa.r1 = 0; sa.n1 = 0; sa.B = nb;
+    DV_LAUNCH("pred_scores", hs, launch_pred_scores(p->wtype, sa, hs));
+    return DV_OK;
+  };
   if (B > 1 && p->wtype == DV_F16) {
     // a batch on fp16 factors: the weights are read once per 32 inputs, on the matrix cores
     // (16 inputs at the OPT-66B predictor: 12 + 21 us against 62 + 190 us with the weights read
-    // once per input)
+    // once per input), but for layers so small that their rows on the matrix cores are a few long chains.
+    // Hidden layer, us once per input / on the matrix cores: 2 inputs, rank 1000, width 9216
+    // 9.9 / 10.7, 3 inputs 14.1 / 10.9; rank 64: 8 inputs 8.0 / 10.0, 16 inputs 12.9 / 11.0. Scores of
+    // rank 1000: 96 heads, 3 inputs 3.9 / 11.9, 16 inputs 5.1 / 12.6; 300 rows, 8 inputs 8.3 / 14.1; rank 400,
+    // 1000 rows: 2 inputs 6.7 / 8.5, 3 inputs 9.6 / 7.8. (The scores' few rows make up for the hidden
+    // layer of 3 inputs. Once per input they take a hidden layer in one part.)
     for (int b = 0; b < B; b += kMaxBatch) {
-      st = batch_scores(p, x + (size_t)b * p->d, min(kMaxBatch, B - b), splits, hid, s + (size_t)b * p->n_out, hs);
+      const int nb = min(kMaxBatch, B - b);
+      const bool few = (long)nb * p->n_out <= 2400;
+      const bool each = nb <= (few ? 3 : 2) || nb * p->r <= 512;
+      const int parts = each ? 1 : splits;
+      st = each ? hidden_each(b, nb) : batch_hidden(p, x + (size_t)b * p->d, nb, parts, hid, hs);
+      if (st != DV_OK) return st;
+      st = few && parts == 1 ? scores_each(b, nb) : batch_scores(p, hid, nb, parts, s + (size_t)b * p->n_out, hs);
       if (st != DV_OK) return st;
     }
   } else {
-    PredHidArgs ha{};
-    ha.d = p->d; ha.B = B; ha.x = x; ha.g = nullptr; ha.be = nullptr; ha.eps = 0.f;
-    ha.AT0 = p->AT; ha.r0 = p->r; ha.hid0 = hid; ha.AT1 = nullptr; ha.r1 = 0; ha.hid1 = nullptr;
-    DV_LAUNCH("pred_hidden", hs, launch_pred_hidden(p->wtype, ha, hs));
-    PredScoreArgs sa{};
-    sa.r0 = p->r; sa.n0 = p->n_out; sa.BT0 = p->BT; sa.hid0 = hid; sa.s0 = s;
-    sa.r1 = 0; sa.n1 = 0; sa.B = B;
-    DV_LAUNCH("pred_scores", hs, launch_pred_scores(p->wtype, sa, hs));
+    st = hidden_each(0, B);
+    if (st != DV_OK) return st;
+    st = scores_each(0, B);
+    if (st != DV_OK) return st;
   }
   DV_LAUNCH("select", hs, launch_select(s, B, p->n_out, mode, k, thresh, idx, cap_idx, count, nullptr, hs));
   return DV_OK;

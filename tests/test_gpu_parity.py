@@ -108,6 +108,30 @@ def test_predict_batch_scores_to_fp32(B, d, r, n):
             assert err < 3e-7, (size, b, err)
 
 
+@pytest.mark.parametrize("B,r,n", [(2, 1000, 1200), (2, 1000, 1201), (3, 400, 800), (3, 400, 801), (8, 64, 300),
+                                   (8, 64, 301), (8, 72, 300), (16, 32, 150), (25, 104, 96), (26, 16, 96), (34, 200, 70),
+                                   (35, 200, 70), (65, 8, 5)])
+def test_predict_batch_small_layers(B, r, n):
+    """A few inputs of small layers are taken one at a time, each layer by its own rule: either side of the rules'
+    lines, in turns of 32 with one, two or three inputs left over. The same bound as above."""
+    d = 520
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B * 1000 + r)
+    rnd = lambda *sh: torch.randn(sh, generator=g, device="cuda")
+    pred = Bd.Predictor((0.02 * rnd(r, d)).half(), (0.02 * rnd(n, r)).half())
+    x = rnd(B, d)
+    ref = (x.double() @ pred.AT.double().T) @ pred.BT.double().T
+    for one_part in (False, True):
+        sc = torch.full((B, n), float("nan"), dtype=torch.float32, device="cuda")
+        nb = 256 * ((B * r * 4 + 255) // 256) + 256 * ((B * n * 4 + 255) // 256)
+        ws = torch.empty(nb if one_part else Bd.predict_workspace_bytes(pred, B), dtype=torch.uint8, device="cuda")
+        Bd.dv_predict_heads(pred, x, 1, scores=sc, ws=ws)
+        _sync()
+        for b in range(B):
+            err = float((sc[b].double() - ref[b]).norm() / ref[b].norm())
+            assert err < 3e-7, (one_part, b, err)
+
+
 @pytest.mark.parametrize("ratio", [1e3, 1e5, 1e8, 1e12, 1e30])
 @pytest.mark.parametrize("B,d,r,n", [(2, 72, 24, 40), (16, 1288, 200, 5000), (20, 392, 1000, 300), (5, 12288, 1016, 131)])
 def test_predict_batch_small_inputs_beside_large_ones(B, d, r, n, ratio):

@@ -498,8 +498,7 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
         for (int tt = 0; tt < TB; ++tt) load_w(wf[tt], tt);
 #pragma unroll
         for (int j = 0; j < NBT; ++j) {
-          float m = 0.f;
-          uint32_t least = ~0u;                        // bits of the smallest magnitude but 0, less one
+          float m = 0.f, least = INFINITY;
 #pragma unroll
           for (int ks = 0; ks < 2 * NBLK; ++ks) {
             const bool in = (2 * kb + ks) * 32 + 8 * lg < s.d;
@@ -508,7 +507,7 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
               const float v = in ? xv[ks][j][e >> 2][e & 3] : 0.f;
               xv[ks][j][e >> 2][e & 3] = v;
               m = fmaxf(m, fabsf(v));
-              least = min(least, (__float_as_uint(v) & 0x7fffffffu) - 1u);
+              least = fminf(least, fabsf(v));
             }
           }
           m = fmaxf(m, __shfl_xor(m, 16, kWave));
@@ -517,21 +516,28 @@ __global__ void __launch_bounds__(kRowsNW * 64) k_rows(RowsArgs a) {
           const int e2 = min(max(140 - (int)((__float_as_uint(m) >> 23) & 255u), -126), 126);
           const float sc = __uint_as_float((uint32_t)(e2 + 127) << 23);
           inv[j] = __uint_as_float((uint32_t)(127 - e2) << 23);
-          wide[j] |= least + 1u < __float_as_uint(0x1p-23f * inv[j]) && least != ~0u;
+          if (__any(least < 0x1p-23f * inv[j])) {                // zeros, as a rule
+#pragma unroll
+            for (int ks = 0; ks < 2 * NBLK; ++ks)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                const float v = xv[ks][j][e >> 2][e & 3];
+                wide[j] |= v != 0.f && fabsf(v) < 0x1p-23f * inv[j];
+              }
+          }
 #pragma unroll
           for (int ks = 0; ks < 2 * NBLK; ++ks) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              const float v = xv[ks][j][e >> 2][e & 3] * sc;
+              const float v = xv[ks][j][e >> 2][e & 3] * sc;   // (infinities and NaN make NaN of the rest)
               const _Float16 hi = (_Float16)v;
-              float rest = (v - (float)hi) * 0x1p11f;
-              rest = fabsf(v) < 32768.f ? rest : 0.f;          // (infinities and NaN: the first term alone)
+              const float rest = fmaf((float)hi, -0x1p11f, v * 0x1p11f);
               const _Float16 mid = (_Float16)rest;
-              bf[ks][j][0][e] = (_Float16)((rest - (float)mid) * 0x1p11f);
+              bf[ks][j][0][e] = (_Float16)fmaf((float)mid, -0x1p11f, rest * 0x1p11f);
               bf[ks][j][TERMS - 2][e] = mid;
               bf[ks][j][TERMS - 1][e] = hi;
             }
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (MT > 1) __builtin_amdgcn_sched_barrier(0);   // (terms made ahead spill)
           }
         }
       } else {

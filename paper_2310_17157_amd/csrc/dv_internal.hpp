@@ -393,6 +393,7 @@ struct PredScoreArgs {
   // scores of the first predictor and writes their top-sel_k0 set, ascending, to
   // sel_set0 (and sel_set0_out if not NULL).
   int sel_k0; int32_t* sel_set0; int32_t* sel_set0_out;
+  bool skew;                         // set by the launcher: fewer rows for the grid's second half
 };
 hipError_t launch_pred_scores(int wtype, const PredScoreArgs& a, hipStream_t st);
 

@@ -173,14 +173,14 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2 
   constexpr int RPG = GPW * RU;        // rows per wavefront group
   const int Gw = (int)gridDim.x - (hosted ? 1 : 0), wg = (int)blockIdx.x - (hosted ? 1 : 0);
   const int rb = hosted ? a.n0 : 0, R = nrows - rb;
-  // Workgroups of the second half start their stream later (they are dispatched
+  // Workgroups past one per CU start their stream later (they are dispatched
   // second, onto CUs whose first workgroup already has its loads in flight, and their
-  // hidden-vector reads queue behind them), so they take 15 % fewer rows than those of
-  // the first half (per-workgroup clocks at the OPT-175B predictors: last end 20.0 ->
-  // 18.9 us; 0.4 us off the launch).
+  // hidden-vector reads queue behind them), so they take 15 % fewer rows than the average and the
+  // first half of the grid 15 % more (per-workgroup clocks at the OPT-175B predictors: last end 20.0 ->
+  // 18.9 us; 0.4 us off the launch). Grids of at most one per CU share the rows evenly.
   auto cum = [&](int i) -> long {
     const int h = Gw / 2;
-    return i <= h ? (long)i * 115 : (long)h * 115 + (long)(i - h) * 85;
+    return !a.skew ? i : (i <= h ? (long)i * 115 : (long)h * 115 + (long)(i - h) * 85);
   };
   const int w0 = rb + (int)((long)R * cum(wg) / cum(Gw)), w1 = rb + (int)((long)R * cum(wg + 1) / cum(Gw));
   const int v0 = w0 + (w1 - w0) * wave / NW, v1 = w0 + (w1 - w0) * (wave + 1) / NW;   // this wavefront's rows
@@ -261,7 +261,7 @@ static hipError_t launch_scores_k(const PredScoreArgs& a, dim3 grid, size_t lds,
 }
 
 template <typename T>
-static hipError_t launch_scores_t(const PredScoreArgs& a, hipStream_t st) {
+static hipError_t launch_scores_t(PredScoreArgs a, hipStream_t st) {
   constexpr int NW = 8;
   constexpr int E = Chunk<T>::E;
   const int nch = max(a.r0, a.r1) / E;
@@ -272,8 +272,9 @@ static hipError_t launch_scores_t(const PredScoreArgs& a, hipStream_t st) {
   // when a wavefront's group (4 * 8 short rows, 2 long ones) per workgroup takes all rows, since
   // short rows are little work for the wavefronts dispatched (3084 rows of 64 fp32: 6.4 -> 5.1 us)
   const int group = nch > 32 ? 2 : (nch > 16 ? 2 * 8 : 4 * 8);
-  const int blocks = max(1, min(2 * device_cu_count() - hosted, (nrows + group - 1) / group));
+  const int blocks = max(1, min(2 * device_cu_count() - hosted, (nrows - hosted * a.n0 + group - 1) / group));
   const dim3 grid(blocks + hosted, a.B);
+  a.skew = blocks + hosted > device_cu_count();
   // hidden vectors staged behind the first loads when one float4 per thread holds them
   const bool early = max(a.r0, a.r1) <= 4 * NW * 64;
   if (nch > 32) {

@@ -58,7 +58,7 @@ def test_batch_mlp_per_sequence_sets(B, mode):
                                      (32, 200, 9000, 4000), (5, 4104, 700, 90)])
 @pytest.mark.parametrize("mode", ["union", "masked"])
 def test_batch_mlp_row_and_width_remainders(B, d, n, k, mode):
-    """Row shares of none, one, part of a tile and several rounds of ten tiles per workgroup,
+    """Row shares of none, one and part of a tile to three tiles per workgroup,
     and widths of one partial 64-element block to 65 blocks over eight wavefronts."""
     cfg = get_config("small_b8").with_(name="rem", B=B, d=d, N=n, k_mlp=k, H=2, dh=8, r=8, k_heads=1, L=4, L_range=(4, 4))
     t = make_layer(cfg, 31, device="cuda", biases=True, with_predictors=False)
@@ -72,6 +72,23 @@ def test_batch_mlp_row_and_width_remainders(B, d, n, k, mode):
     ref = O.mlp_batch(host(t["x"]), m["W1T"], m["b1"], m["W2T"], m["b2"], [s.tolist() for s in sets], mode)
     for b in range(B):
         assert rel_l2(host(out)[b], ref[b]) < REL_TOL, (b, rel_l2(host(out)[b], ref[b]))
+
+
+@pytest.mark.parametrize("B", [3, 20])
+def test_batch_mlp_second_round_of_tiles(B):
+    """50000 rows of the union: more than ten 16-row tiles for each workgroup of one per CU, so that each takes
+    its rows in two rounds (registers, LDS sums and row numbers anew)."""
+    n = 50000
+    cfg = get_config("small_b8").with_(name="rounds", B=B, d=72, N=n, k_mlp=n, H=2, dh=8, r=8, k_heads=1, L=4, L_range=(4, 4))
+    t = make_layer(cfg, 35, device="cuda", biases=True, with_predictors=False)
+    t["x"] = t["x"] * 50.0
+    out = Bd.dv_sparse_mlp(_mlp(t), t["x"], torch.arange(n, dtype=torch.int32, device="cuda"), idx_per_seq=0)
+    _sync()
+    m = oracle_mlp(t)
+    x = host(t["x"])
+    for b in range(B):
+        ref = O.mlp_dense(x[b], m["W1T"], m["b1"], m["W2T"], m["b2"])
+        assert rel_l2(host(out)[b], ref) < REL_TOL, (b, rel_l2(host(out)[b], ref))
 
 
 @pytest.mark.parametrize("offset", [1, 2, 3])
@@ -223,6 +240,21 @@ def test_batch_attn_all_heads_and_pos0():
     _check_attn(cfg, t, heads, out, K0, V0)
 
 
+@pytest.mark.parametrize("B", [2, 17])
+def test_batch_attn_second_round_of_tiles(B):
+    """43008 Q/K/V rows, of all 112 heads of 128: the row launch takes them in two rounds of tiles."""
+    cfg = get_config("small_b8").with_(name="rounds_attn", B=B, d=72, N=64, k_mlp=8, H=112, dh=128, r=8, k_heads=112,
+                                       L=5, L_range=(1, 5))
+    t = make_layer(cfg, 36, device="cuda", biases=True)
+    t["x"] = t["x"] * 50.0
+    K0, V0 = host(t["K"]).copy(), host(t["V"]).copy()
+    heads = np.tile(np.arange(cfg.H, dtype=np.int32), (B, 1))
+    attn, _, _, _, kv, _ = layer_objects(t, cfg.H)
+    out = Bd.dv_sparse_attn(attn, t["x"], kv, torch.tensor(heads, device="cuda"), 1.0 / np.sqrt(cfg.dh))
+    _sync()
+    _check_attn(cfg, t, heads, out, K0, V0)
+
+
 def test_batch_attn_no_heads_is_bias():
     cfg = _cfg("small_b8")
     t = make_layer(cfg, 33, device="cuda", biases=True)
@@ -272,6 +304,19 @@ def test_batch_block(B, mode, batch_mode):
                                      batch_mode=Bd.DV_MLP_UNION if batch_mode == "union" else Bd.DV_MLP_MASKED)
     _sync()
     _check_block(cfg, t, out, hs, ms, K0, V0, mode, batch_mode)
+
+
+@pytest.mark.parametrize("B", [5, 18])
+def test_batch_block_second_round_of_tiles(B):
+    """A batched layer of 50000 neurons, whose predictor scores take two rounds of tiles per workgroup."""
+    cfg = get_config("small_b8").with_(name="rounds_block", B=B, d=72, N=50000, k_mlp=300, H=8, dh=16, r=24, k_heads=3,
+                                       L=9, L_range=(3, 9))
+    t = make_layer(cfg, 43, device="cuda", biases=True, ln_random=True)
+    K0, V0 = host(t["K"]).copy(), host(t["V"]).copy()
+    attn, mlp, ph, pm, kv, ln = layer_objects(t, cfg.H)
+    out, hs, ms = Bd.dv_sparse_block(attn, mlp, ph, pm, ln, kv, t["x"], cfg.k_heads, cfg.k_mlp, 1.0 / np.sqrt(cfg.dh))
+    _sync()
+    _check_block(cfg, t, out, hs, ms, K0, V0, "lookahead", "union")
 
 
 @pytest.mark.parametrize("B,H", [(2, 3), (32, 32), (8, 33), (32, 256), (31, 256), (5, 260)])

@@ -108,6 +108,25 @@ def test_predict_batch_scores_to_fp32(B, d, r, n):
             assert err < 3e-7, (size, b, err)
 
 
+@pytest.mark.parametrize("B,n", [(5, 50000), (20, 40000)])
+def test_predict_batch_second_round_of_tiles(B, n):
+    """More than nine 16-row tiles for each workgroup that shares a batch's score rows (17 to 32 inputs are two
+    workgroups for each share): the rows are taken in rounds. The same bound as above."""
+    d, r = 64, 8
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B)
+    rnd = lambda *sh: torch.randn(sh, generator=g, device="cuda")
+    pred = Bd.Predictor((0.02 * rnd(r, d)).half(), (0.02 * rnd(n, r)).half())
+    x = rnd(B, d)
+    sc = torch.full((B, n), float("nan"), dtype=torch.float32, device="cuda")
+    Bd.dv_predict_mlp(pred, x, 7, scores=sc)
+    ref = (x.double() @ pred.AT.double().T) @ pred.BT.double().T
+    _sync()
+    for b in range(B):
+        err = float((sc[b].double() - ref[b]).norm() / ref[b].norm())
+        assert err < 3e-7, (b, err)
+
+
 @pytest.mark.parametrize("B,r,n", [(2, 1000, 1200), (2, 1000, 1201), (3, 400, 800), (3, 400, 801), (8, 64, 300),
                                    (8, 64, 301), (8, 72, 300), (16, 32, 150), (25, 104, 96), (26, 16, 96), (34, 200, 70),
                                    (35, 200, 70), (65, 8, 5)])
@@ -257,13 +276,14 @@ def test_select_slots_per_thread(n):
     """The register select keeps 4 to 60 scores per thread by the vector's length (to 61440
     scores), its padding slots counted up to 1024 of them: at and beside those lengths, for two rows (the second
     one misaligned when n is not a multiple of 4) of few distinct values, so that the
-    boundary ties, and a set of -inf, +inf, zeros of both signs and NaN-free extremes."""
+    boundary ties, with infinities, the largest finite values and a subnormal among them."""
     d, r = 64, 8
     AT = torch.zeros((r, d), dtype=torch.float32, device="cuda")
     AT[0, 0] = 1.0
     BT = torch.zeros((n, r), dtype=torch.float32, device="cuda")
     vals = torch.tensor([float((i * 37) % 211) - 100.0 for i in range(n)])
     vals[5], vals[n - 1], vals[n // 2], vals[0] = 3e38, -3e38, -0.0, 1e-45
+    vals[6], vals[n - 2], vals[n - 3] = float("inf"), -float("inf"), float("inf")
     BT[:, 0] = vals.cuda()
     x = torch.zeros((2, d), dtype=torch.float32, device="cuda")
     x[0, 0], x[1, 0] = 1.0, -1.0

@@ -280,7 +280,11 @@ hipError_t launch_axpy(int wtype, const AxpyArgs& a, hipStream_t st) {
   // Few rows: a workgroup per 128-byte column tile takes all of them (8 rows per load), so no
   // split sum follows, whose stores, ticket and reads are a chain of about 2 us: 256 fp32 head
   // rows of 768 columns 7.5 -> 5.4 us, 307 neuron rows 5.3 -> 4.5. With more rows the tiles are too
-  // few and long (4096 columns: 1536 head rows 10.8 -> 14.6 us).
+  // few and long (4096 columns: 1536 head rows 10.8 -> 14.6 us). The line, over widths 512 to 12288 in
+  // both types: up to 512 rows whole tiles are faster (fp16 neuron rows of 9216 columns, split / whole: 512 rows
+  // 8.2 / 6.0) but for fp32 rows past 8192 columns, whose tiles outnumber the CUs (12288 columns: 256 rows
+  // 6.4 / 5.2, 512 rows 7.8 / 8.3); at 1024 rows the split ones, most clearly with head rows (1288 columns 7.7 / 10.9,
+  // 4096 9.5 / 9.8, fp32 12288 13.4 / 16.7).
   if (a.nrows > 0 && a.nrows <= kAxpyWholeRows) {
     if (a.dh > 0)
       return wtype == DV_F16 ? launch_axpy_t<_Float16, true, 8, 4, 8>(a, st, true)

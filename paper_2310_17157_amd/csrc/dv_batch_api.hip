@@ -253,7 +253,8 @@ size_t batch_block_ws(const dv_attn* a, const dv_mlp* m, const dv_predictor* pa,
   return bblock_layout(a, m, pa, pm, B, kh, km, w, &o);
 }
 
-// The largest predictor rank of a batched layer.
+// The largest predictor rank of a batched layer. (No kernel needs the limit: the row launches take rows of
+// any length. It is what the entry point has accepted.)
 int batch_max_rank(int B) { return B <= 16 ? 3072 : 1536; }
 
 // Predictor hidden layers (one or two predictors on the same x16) and their scores.
@@ -316,7 +317,7 @@ dv_status batch_block(const dv_attn* a, const dv_mlp* m, const dv_predictor* pa,
   if (st != DV_OK) return st;
   // One launch selects the neurons and, in one more workgroup, the heads with their union: one
   // after the other those were three (3.9 + 8.5 + 6.4 us for 8 sequences at the OPT-6.7B shapes).
-  const bool fused = kh > 0 && head_sets_fit(B, a->H);
+  const bool fused = kh > 0 && head_sets_fit(a->H);
   if (fused) {
     HeadSets h{};
     h.s = o.s_h; h.B = B; h.H = a->H; h.k = kh; h.sets = o.heads; h.sets2 = heads_out;

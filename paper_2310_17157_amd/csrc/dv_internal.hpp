@@ -345,6 +345,9 @@ inline void launch_k(void (*kern)(P...), dim3 grid, dim3 block, size_t lds, hipS
     if (dv_e_ != hipSuccess) return DV_ERR_HIP;     \
   } while (0)
 
+// Largest batch of the batched (matrix-core) path: token columns of one MFMA tile pair.
+constexpr int kMaxBatch = 32;
+
 // ---------------------------------------------------------- launchers
 // Each returns hipSuccess or the launch error. All work goes on `st`.
 
@@ -353,17 +356,16 @@ hipError_t launch_select(const float* scores, int B, int n, int mode, int k, flo
                          int32_t* idx, int cap, int32_t* count, int32_t* idx2, hipStream_t st);
 
 // A batch's head sets (top-k of each row of s [B][H]) and their union (launch_union's U, count
-// and slot) by one workgroup, whose work per key is H: up to 256 heads and the keys that fit
+// and slot) by one workgroup, whose work per key is H: up to 256 heads, whose keys for kMaxBatch rows fit
 // its LDS.
 struct HeadSets {
   const float* s; int B, H, k;
   int32_t* sets; int32_t* sets2;     // [B][k], ascending; sets2 may be NULL
   int32_t* U; int32_t* count; int32_t* slot;
 };
-constexpr int kHeadSetKeys = 8192, kHeadSetBits = 512;   // words of LDS
-inline bool head_sets_fit(int B, int H) {
-  return H <= 256 && B * H <= kHeadSetKeys && B * ((H >> 5) + 1) <= kHeadSetBits;
-}
+constexpr int kHeadSetMax = 256;
+constexpr int kHeadSetKeys = kMaxBatch * kHeadSetMax, kHeadSetBits = kMaxBatch * ((kHeadSetMax >> 5) + 1);   // words of LDS
+inline bool head_sets_fit(int H) { return H <= kHeadSetMax; }
 // They and (n > 0) the top-k sets of scores [B][n] in one launch.
 hipError_t launch_select_heads(const HeadSets& heads, const float* scores, int n, int k, int32_t* idx, int32_t* idx2,
                                hipStream_t st);
@@ -423,9 +425,6 @@ struct QkvArgs {
   int32_t* list; int list_stride; int32_t* list_count;
 };
 hipError_t launch_qkv(int wtype, int kvtype, const QkvArgs& a, hipStream_t st);
-
-// Largest batch of the batched (matrix-core) path: token columns of one MFMA tile pair.
-constexpr int kMaxBatch = 32;
 
 // Split-KV decode attention for the selected heads of B sequences (grid z = sequence).
 struct AttnArgs {

@@ -201,6 +201,12 @@ __device__ __forceinline__ void wg_select(const float* __restrict__ s, int n, in
   __syncthreads();
 }
 
+// Every finite or infinite float maps above kLeastKey; with RAISE the negative NaN that map
+// below it are raised to it.
+constexpr uint32_t kLeastKey = 1u << 19;
+template <bool RAISE>
+__device__ __forceinline__ uint32_t slot_key(float f) { return RAISE ? max(fkey(f), kLeastKey) : fkey(f); }
+
 // The same selection with every key held in registers. Wavefront w owns the
 // contiguous segment [w*64*IPT, (w+1)*64*IPT); within it lane l holds, for each
 // group g < IPT/4, the four keys at w*64*IPT + 256*g + 4*l + (0..3), so every load
@@ -210,21 +216,17 @@ __device__ __forceinline__ void wg_select(const float* __restrict__ s, int n, in
 // further memory round trips. Requires n <= NT * IPT.
 //
 // Slots past n hold key 0, below every finite or infinite score's, so they never match a selected
-// prefix and need no separate validity test (k >= n, where every score is taken, writes 0..n-1 directly). They are
-// kept out of the first histogram where they are many (PAD): counted, they all fall in one bin, and the LDS
-// atomics of one address run a lane at a time (3072 scores in 48 slots per thread: 55 us
-// for the launch that hosts the selection, 16384 scores: 38.6 us). With little padding
-// the predicate is left out, 1.6 us less at 49152 scores. The negative NaN of the largest payloads
-// map to that key or share its 13-bit prefix: kept out, the padding must not be confused with them, so
-// their keys are raised past that prefix (0.4 us at 53248 scores); counted, it comes after them in index order. The selection
-// boundary is re-read from LDS,
-// wavefront-uniform, before the write walk, so the compiler recomputes the per-key
-// predicates instead of keeping them live across the scans.
-// Every finite or infinite float maps above kLeastKey; with RAISE the negative NaN that map below it are raised to it.
-constexpr uint32_t kLeastKey = 1u << 19;
-template <bool RAISE>
-__device__ __forceinline__ uint32_t slot_key(float f) { return RAISE ? max(fkey(f), kLeastKey) : fkey(f); }
-
+// prefix and need no separate validity test (k >= n, where every score is taken, writes
+// 0..n-1 directly). They are kept out of the first histogram where they are many (PAD):
+// counted, they all fall in one bin, and the LDS atomics of one address run a lane at a
+// time (3072 scores in 48 slots per thread: 55 us for the launch that hosts the selection,
+// 16384 scores: 38.6 us). With little padding the predicate is left out, 1.6 us less at
+// 49152 scores. The negative NaN of the largest payloads map to that key or share its
+// 13-bit prefix: kept out, the padding must not be confused with them, so their keys are
+// raised past that prefix (0.4 us at 53248 scores); counted, it comes after them in index
+// order. The selection boundary is re-read from LDS, wavefront-uniform, before the write
+// walk, so the compiler recomputes the per-key predicates instead of keeping them live
+// across the scans.
 template <int NT, int IPT, bool OVERLAP, bool PAD>
 __device__ __forceinline__ void wg_select_reg(const float* __restrict__ s, int n, int mode, int k, float thresh,
                               int32_t* __restrict__ out, int cap, int32_t* __restrict__ count_out,
@@ -504,7 +506,9 @@ __device__ void wg_select_small(const float* __restrict__ s, int n, int mode, in
 // for the predictor's call, in registers 30). A call takes the fewest that hold
 // its scores (as a launch of its own any multiple of 4, hosted 4, 16, 48 or 60), so that every
 // wavefront has a share of a short vector: with 48 slots the first wavefront alone would
-// hold 3072 scores and walk them serially.
+// hold 3072 scores and walk them serially. In steps of 4 / only 4, 8, 16, 32, 48, 60 / only 4, 16, 48, 60 the launch
+// takes, in us: 12288 scores 7.4 / 8.0 / 8.0, 20480 8.9 / 11.0 / 16.3, 28672 10.8 / 12.0 / 18.0, 36864
+// 12.6 / 18.2 / 18.2, 45056 14.0 / 18.9 / 18.8, 53248 19.4 / 22.4 / 22.4.
 constexpr int kSelIPT = 60;
 // Padding slots up to which their count in one bin (about 1 ns each) costs less than keeping
 // them out.
@@ -555,9 +559,10 @@ __device__ __forceinline__ void wg_head_sets(const HeadSets& a, uint32_t* keys, 
 // Top-k selection run by one extra workgroup of another kernel's launch (which leaves
 // CUs free for it), so that the selection runs beside that kernel's weight stream
 // instead of on the critical path. Inlined: as a call it needs a stack frame for the
-// callee-saved registers besides its own spills, which raised the host kernel's
-// private segment to 336 bytes per lane and its duration by 1.5-2 us on the
-// 3 x 4096-row QKV launch (inlined: 120 bytes).
+// callee-saved registers (336 bytes per lane of private segment in the host kernel), which took
+// 1.5-2 us longer on the 3 x 4096-row QKV launch. Inlined the host kernel has no private segment
+// (126 vector registers), so four slot counts are what it takes: a kernel each, as the
+// selection's own launch has them, it cannot have.
 // Up to kSelIPT * NT scores are selected from registers, larger score vectors stream from
 // memory. smem: kSelBins u32 plus kSelSm(NT) ints of LDS.
 

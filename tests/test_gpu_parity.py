@@ -344,7 +344,7 @@ def test_block_nan_predictor_scores_stay_in_range():
 
 
 def test_select_register_path_large_sets():
-    """Register-resident selection (n <= 49152) of sets too large to stage in LDS
+    """Register-resident selection (n <= 61440) of sets too large to stage in LDS
     (more than 8128 members) is written straight to memory: top-k with and without a
     tie at the boundary, and threshold mode with the count above the capacity."""
     n = 40000
@@ -373,7 +373,7 @@ def test_select_register_path_large_sets():
 
 
 def test_select_streaming_path_agrees_with_oracle():
-    """More than 49152 scores do not fit the registers of one workgroup: the radix
+    """More than 61440 scores do not fit the registers of one workgroup: the radix
     select streams them from memory in every pass. Exact ties, top-k and threshold."""
     n = 100000
     d, r = 64, 8

@@ -49,7 +49,8 @@ __device__ __forceinline__ v4s_t ds_read_tr16(const _Float16* p) {
 // its offset, the marks inside it the ranks. U[offset + rank] = the members in
 // ascending order, *count = their number (last chunk), and optionally
 // mask[offset + rank] = the member's sets as bits (bit b: set b holds it), gathered
-// by LDS atomics on one word per index of the chunk.
+// by LDS atomics on one word per index of the chunk. Optionally also slot[b][i] = i's place
+// in set b, or -1 (each workgroup for its chunk).
 constexpr int kUnionChunk = 2048;
 constexpr int kUnionNT = 1024;
 static_assert(kUnionChunk == 2 * kUnionNT, "two indices of the chunk per thread");
@@ -97,29 +98,24 @@ __device__ __forceinline__ void union_chunk(const int32_t* __restrict__ sets, in
                                             uint32_t* ush) {
   __shared__ int red[kUnionNT / 64 + 1];
   const int tid = threadIdx.x;
-  // slot[b][i] = i's place in set b or -1: each entry also clears the gap before it
-  if (slot != nullptr && c == nc - 1)
-    for (int e = tid; e < B * k; e += kUnionNT) {
-      const int b = e / k, j = e - b * k, v = min(max(sets[e], 0), n - 1);
-      int32_t* sl = slot + (size_t)b * n;
-      for (int i = j == 0 ? 0 : min(max(sets[e - 1], -1), n - 1) + 1; i < v; ++i) sl[i] = -1;
-      sl[v] = j;
-      if (j == k - 1)
-        for (int i = v + 1; i < n; ++i) sl[i] = -1;
-    }
   const int lo = c * kUnionChunk, hi = min(n, lo + kUnionChunk);
   const int n16 = (n + 15) & ~15;
   uint8_t* mk = reinterpret_cast<uint8_t*>(ush);
   uint32_t* mw = ush + n16 / 4;
   const int nq = ((hi + 15) & ~15) / 16;   // marks read below: [0, round_up(hi, 16))
   for (int q = tid; q < nq; q += kUnionNT) reinterpret_cast<uint4*>(mk)[q] = make_uint4(0u, 0u, 0u, 0u);
-  if (MASK)
+  const bool words = MASK || slot != nullptr;
+  if (words)
     for (int i = tid; i < kUnionChunk; i += kUnionNT) mw[i] = 0u;
   __syncthreads();
   union_scan(sets, B * k, [&](int e, int v) {
     if ((unsigned)v < (unsigned)hi) {
       mk[v] = 1;
-      if (MASK && v >= lo) atomicOr(&mw[v - lo], 1u << (e / k));
+      if (words && v >= lo) {
+        const int b = e / k;
+        atomicOr(&mw[v - lo], 1u << b);
+        if (slot != nullptr) slot[(size_t)b * n + v] = e - b * k;
+      }
     }
   });
   __syncthreads();
@@ -145,6 +141,13 @@ __device__ __forceinline__ void union_chunk(const int32_t* __restrict__ sets, in
     if (MASK) mask[r + f0] = mw[i0 + 1 - lo];
   }
   if (c == nc - 1 && tid == 0) *count = before + in_chunk;
+  // the chunk's places that no entry has written, every thread some (each entry clearing the gap before
+  // its own is a serial chain: 10.5 us for the launch at 32 sets of 2 of 96 heads against 7.2)
+  if (slot != nullptr)
+    for (int e = tid; e < B * (hi - lo); e += kUnionNT) {
+      const int b = e / (hi - lo), i = e - b * (hi - lo);
+      if (!((mw[i] >> b) & 1u)) slot[(size_t)b * n + lo + i] = -1;
+    }
 }
 
 template <bool MASK>

@@ -89,9 +89,9 @@ __device__ __forceinline__ void union_scan(const int32_t* __restrict__ sets, int
 // Sum of four 0/1 bytes.
 __device__ __forceinline__ int byte_flags(uint32_t w) { return (int)((w * 0x01010101u) >> 24); }
 
-// Chunk c of nc; ush: dynamic LDS, marks [round_up(n, 16)] bytes, then (mask only)
+// Chunk c of nc; ush: dynamic LDS, marks [round_up(n, 16)] bytes, then (mask and slot only)
 // kUnionChunk words.
-template <bool MASK>
+template <bool MASK, bool SLOT>
 __device__ __forceinline__ void union_chunk(const int32_t* __restrict__ sets, int B, int k, int n,
                                             int32_t* __restrict__ U, int32_t* __restrict__ count,
                                             uint32_t* __restrict__ mask, int32_t* __restrict__ slot, int c, int nc,
@@ -104,7 +104,7 @@ __device__ __forceinline__ void union_chunk(const int32_t* __restrict__ sets, in
   uint32_t* mw = ush + n16 / 4;
   const int nq = ((hi + 15) & ~15) / 16;   // marks read below: [0, round_up(hi, 16))
   for (int q = tid; q < nq; q += kUnionNT) reinterpret_cast<uint4*>(mk)[q] = make_uint4(0u, 0u, 0u, 0u);
-  const bool words = MASK || slot != nullptr;
+  constexpr bool words = MASK || SLOT;
   if (words)
     for (int i = tid; i < kUnionChunk; i += kUnionNT) mw[i] = 0u;
   __syncthreads();
@@ -114,7 +114,7 @@ __device__ __forceinline__ void union_chunk(const int32_t* __restrict__ sets, in
       if (words && v >= lo) {
         const int b = e / k;
         atomicOr(&mw[v - lo], 1u << b);
-        if (slot != nullptr) slot[(size_t)b * n + v] = e - b * k;
+        if (SLOT) slot[(size_t)b * n + v] = e - b * k;
       }
     }
   });
@@ -143,19 +143,26 @@ __device__ __forceinline__ void union_chunk(const int32_t* __restrict__ sets, in
   if (c == nc - 1 && tid == 0) *count = before + in_chunk;
   // the chunk's places that no entry has written, every thread some (each entry clearing the gap before
   // its own is a serial chain: 10.5 us for the launch at 32 sets of 2 of 96 heads against 7.2)
-  if (slot != nullptr)
+  if (SLOT)
     for (int e = tid; e < B * (hi - lo); e += kUnionNT) {
       const int b = e / (hi - lo), i = e - b * (hi - lo);
       if (!((mw[i] >> b) & 1u)) slot[(size_t)b * n + lo + i] = -1;
     }
 }
 
-template <bool MASK>
+template <bool MASK, bool SLOT>
 __global__ void __launch_bounds__(kUnionNT) k_union(const int32_t* __restrict__ sets, int B, int k, int n,
                                                     int32_t* __restrict__ U, int32_t* __restrict__ count,
                                                     uint32_t* __restrict__ mask, int32_t* __restrict__ slot) {
   extern __shared__ __attribute__((aligned(16))) uint32_t ush[];
-  union_chunk<MASK>(sets, B, k, n, U, count, mask, slot, blockIdx.x, gridDim.x, ush);
+  union_chunk<MASK, SLOT>(sets, B, k, n, U, count, mask, slot, blockIdx.x, gridDim.x, ush);
+}
+
+// The kernel of a union without mask and slot, with mask, or with slot. (Chosen inside, the scan
+// of 32 sets of 2457 without either took 2 us longer.)
+template <class K>
+static K union_form(const uint32_t* mask, const int32_t* slot, K none, K masked, K slotted) {
+  return mask != nullptr ? masked : (slot != nullptr ? slotted : none);
 }
 
 size_t union_lds_bytes(int n) { return (size_t)((n + 15) & ~15) + (size_t)kUnionChunk * 4; }
@@ -164,14 +171,11 @@ hipError_t launch_union(const int32_t* sets, int B, int k, int n, int32_t* U, in
                         int32_t* slot, hipStream_t st) {
   const int nc = (n + kUnionChunk - 1) / kUnionChunk;
   const size_t lds = union_lds_bytes(n);
-  const void* kern = mask != nullptr ? reinterpret_cast<const void*>(k_union<true>)
-                                     : reinterpret_cast<const void*>(k_union<false>);
-  const hipError_t e = ensure_dyn_lds(kern, lds);
+  if (mask != nullptr && slot != nullptr) return hipErrorInvalidValue;
+  const auto kern = union_form(mask, slot, k_union<false, false>, k_union<true, false>, k_union<false, true>);
+  const hipError_t e = ensure_dyn_lds(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
-  if (mask != nullptr)
-    launch_k(k_union<true>, dim3(nc), dim3(kUnionNT), lds, st, sets, B, k, n, U, count, mask, slot);
-  else
-    launch_k(k_union<false>, dim3(nc), dim3(kUnionNT), lds, st, sets, B, k, n, U, count, mask, slot);
+  launch_k(kern, dim3(nc), dim3(kUnionNT), lds, st, sets, B, k, n, U, count, mask, slot);
   return hipGetLastError();
 }
 
@@ -232,7 +236,7 @@ __global__ void __launch_bounds__(1024) k_ln_cast(const float* __restrict__ x, i
 
 // The cast and the union of the batch's sets in one launch (they are independent):
 // workgroups [0, NB) cast row b, the next nc take union chunk c.
-template <bool MASK>
+template <bool MASK, bool SLOT>
 __global__ void __launch_bounds__(1024) k_cast_union(const float* __restrict__ x, int B, int d, int Kpad,
                                                      const float* __restrict__ g, const float* __restrict__ be,
                                                      float eps, _Float16* __restrict__ X16, int NB,
@@ -243,7 +247,7 @@ __global__ void __launch_bounds__(1024) k_cast_union(const float* __restrict__ x
   if ((int)blockIdx.x < NB)
     ln_cast_row(x, B, d, Kpad, g, be, eps, X16, blockIdx.x, NB);
   else
-    union_chunk<MASK>(sets, B, k, n, U, count, mask, slot, (int)blockIdx.x - NB, nc, ush);
+    union_chunk<MASK, SLOT>(sets, B, k, n, U, count, mask, slot, (int)blockIdx.x - NB, nc, ush);
 }
 
 hipError_t launch_ln_cast(const float* x, int B, int NB, int d, int Kpad, const float* g, const float* be, float eps,
@@ -258,16 +262,12 @@ hipError_t launch_cast_union(const float* x, int B, int NB, int d, int Kpad, con
   static_assert(kUnionNT == 1024, "the cast and the union share the workgroup size");
   const int nc = (n + kUnionChunk - 1) / kUnionChunk;
   const size_t lds = union_lds_bytes(n);
-  const void* kern = mask != nullptr ? reinterpret_cast<const void*>(k_cast_union<true>)
-                                     : reinterpret_cast<const void*>(k_cast_union<false>);
-  const hipError_t e = ensure_dyn_lds(kern, lds);
+  if (mask != nullptr && slot != nullptr) return hipErrorInvalidValue;
+  const auto kern = union_form(mask, slot, k_cast_union<false, false>, k_cast_union<true, false>, k_cast_union<false, true>);
+  const hipError_t e = ensure_dyn_lds(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
-  if (mask != nullptr)
-    launch_k(k_cast_union<true>, dim3(NB + nc), dim3(1024), lds, st, x, B, d, Kpad, g, be, eps, X16, NB,
-                       sets, k, n, U, count, mask, slot, nc);
-  else
-    launch_k(k_cast_union<false>, dim3(NB + nc), dim3(1024), lds, st, x, B, d, Kpad, g, be, eps, X16, NB,
-                       sets, k, n, U, count, mask, slot, nc);
+  launch_k(kern, dim3(NB + nc), dim3(1024), lds, st, x, B, d, Kpad, g, be, eps, X16, NB, sets, k, n, U, count, mask, slot,
+           nc);
   return hipGetLastError();
 }
 
@@ -733,6 +733,17 @@ static hipError_t launch_rows_t(RowsArgs a, hipStream_t st) {
     if constexpr (MODE == kRowsIdentity)
       if (a.src[1].W0 == nullptr && a.src[0].nrows <= 16 * G)
         return launch_rows_v<NB, MODE, EPI, XF32, KT, 1, NB == 16 ? 8 : 4, 1>(a, G, st);
+    // Gathered rows, at most four tiles per workgroup by the sets' sizes: few sums are held, and the
+    // loads of all tiles (with 32 tokens of two) go together. Whole calls, the general form / this one, us:
+    // 16 sequences with 2 of 72 heads of width 9216 75.4 / 74.1, 17 with one 64.4 / 60.8, 2 with 4 of 32 heads
+    // of width 4096 40.1 / 37.6, 8 MLPs of 100 neurons of width 9216 30.4 / 28.8. (Superblocks of eight
+    // instead: 72.3, 60.8, 38.3, 30.7.)
+    if constexpr (MODE != kRowsIdentity) {
+      const RowsSrc& s = a.src[0];
+      const long most = MODE == kRowsHeads ? 3L * min(s.list_max, a.B * a.n_heads) * s.dh : (long)s.list_max;
+      if (most <= 16L * 4 * G)
+        return launch_rows_v<NB, MODE, EPI, XF32, KT, 4, 4, NB == 16 ? 4 : 2>(a, G, st);
+    }
     return launch_rows_v<NB, MODE, EPI, XF32, KT, 10, 4, NB == 16 ? 2 : 1>(a, G, st);
   }
 }

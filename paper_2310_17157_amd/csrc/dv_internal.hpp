@@ -526,7 +526,7 @@ hipError_t launch_fc1(int wtype, const Fc1Args& a, hipStream_t st);
 // ------------------------------------------------ batched (matrix-core) path
 // Union of B ascending sets in [0, n): U ascending, *count and optional membership
 // bits mask[u] (bit b: U[u] is in set b). Needs union_lds_bytes(n) of LDS per
-// workgroup (no scratch memory). slot (optional, [B][n]): i's place in set b, or -1.
+// workgroup (no scratch memory). slot (optional, without mask; [B][n]): i's place in set b, or -1.
 size_t union_lds_bytes(int n);
 hipError_t launch_union(const int32_t* sets, int B, int k, int n, int32_t* U, int32_t* count, uint32_t* mask,
                         int32_t* slot, hipStream_t st);

@@ -74,11 +74,11 @@ def test_batch_mlp_row_and_width_remainders(B, d, n, k, mode):
         assert rel_l2(host(out)[b], ref[b]) < REL_TOL, (b, rel_l2(host(out)[b], ref[b]))
 
 
-@pytest.mark.parametrize("B", [3, 20])
-def test_batch_mlp_second_round_of_tiles(B):
+@pytest.mark.parametrize("B,n", [(3, 50000), (20, 50000), (3, 16384), (20, 16384), (3, 16385), (20, 16385)])
+def test_batch_mlp_second_round_of_tiles(B, n):
     """50000 rows of the union: more than ten 16-row tiles for each workgroup of one per CU, so that each takes
-    its rows in two rounds (registers, LDS sums and row numbers anew)."""
-    n = 50000
+    its rows in two rounds (registers, LDS sums and row numbers anew). And 256 x 64 rows, the most that the
+    form for few rows takes with 256 CUs, and one more."""
     cfg = get_config("small_b8").with_(name="rounds", B=B, d=72, N=n, k_mlp=n, H=2, dh=8, r=8, k_heads=1, L=4, L_range=(4, 4))
     t = make_layer(cfg, 35, device="cuda", biases=True, with_predictors=False)
     t["x"] = t["x"] * 50.0

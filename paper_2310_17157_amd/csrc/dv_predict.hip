@@ -467,11 +467,13 @@ static dv_status predict_impl(const dv_predictor* p, const float* x, int32_t B, 
     // 9.9 / 10.7, 3 inputs 14.1 / 10.9; rank 64: 8 inputs 8.0 / 10.0, 16 inputs 12.9 / 11.0. Scores of
     // rank 1000: 96 heads, 3 inputs 3.9 / 11.9, 16 inputs 5.1 / 12.6; 300 rows, 8 inputs 8.3 / 14.1; rank 400,
     // 1000 rows: 2 inputs 6.7 / 8.5, 3 inputs 9.6 / 7.8. (The scores' few rows make up for the hidden
-    // layer of 3 inputs. Once per input they take a hidden layer in one part.)
+    // layer of 3 inputs, of 4 up to 4 Mi weights: rank 1000, width 4096 8.3 / 6.3, 12288 19.1 / 12.3; of
+    // 8 of rank 128: 13.8 / 11.5. Once per input they take a hidden layer in one part.)
     for (int b = 0; b < B; b += kMaxBatch) {
       const int nb = min(kMaxBatch, B - b);
       const bool few = (long)nb * p->n_out <= 2400;
-      const bool each = nb <= (few ? 3 : 2) || nb * p->r <= 512;
+      const bool small = (long)p->r * p->d <= (4 << 20);
+      const bool each = nb <= (few ? (small ? 4 : 3) : 2) || nb * p->r <= (few ? 1024 : 512);
       const int parts = each ? 1 : splits;
       st = each ? hidden_each(b, nb) : batch_hidden(p, x + (size_t)b * p->d, nb, parts, hid, hs);
       if (st != DV_OK) return st;

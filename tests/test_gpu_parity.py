@@ -127,8 +127,8 @@ def test_predict_batch_second_round_of_tiles(B, n):
         assert err < 3e-7, (b, err)
 
 
-@pytest.mark.parametrize("B,r,n", [(2, 1000, 1200), (2, 1000, 1201), (3, 400, 800), (3, 400, 801), (8, 64, 300),
-                                   (8, 64, 301), (8, 72, 300), (16, 32, 150), (25, 104, 96), (26, 16, 96), (34, 200, 70),
+@pytest.mark.parametrize("B,r,n", [(2, 1000, 1200), (2, 1000, 1201), (3, 400, 800), (3, 400, 801), (4, 400, 600), (4, 400, 601), (8, 64, 300),
+                                   (8, 64, 301), (8, 72, 300), (8, 128, 300), (8, 136, 300), (16, 32, 150), (25, 104, 96), (26, 16, 96), (34, 200, 70),
                                    (35, 200, 70), (65, 8, 5)])
 def test_predict_batch_small_layers(B, r, n):
     """A few inputs of small layers are taken one at a time, each layer by its own rule: either side of the rules'

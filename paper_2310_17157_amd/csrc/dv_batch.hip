@@ -283,7 +283,7 @@ hipError_t launch_cast_union(const float* x, int B, int NB, int d, int Kpad, con
 // memory and a finishing launch (batch 32, OPT-175B shapes, us): QKV 146.5 + 11.7, fc1 of
 // 24950 rows 107.6 + 6.8; batch 8 at the OPT-6.7B shapes, where whole groups of workgroups had
 // no rows: predictor first layer 16.9 + 6.6, scores 22.4, QKV 24.9 + 4.9, fc1 19.2 + 4.5. This
-// form: QKV 158, fc1 104; first layer 8.3, scores 11.5, QKV 24.3, fc1 13.1.
+// form: QKV 158, fc1 104; first layer 8.1, scores 11.2, QKV 22.5, fc1 12.9.
 //
 // Per tile, each load instruction fetches whole 128-byte lines (8 rows x 8 lanes x 16
 // bytes): fetching the MFMA operand layout straight from memory (16 rows x 64 bytes per
@@ -720,15 +720,15 @@ static hipError_t launch_rows_t(RowsArgs a, hipStream_t st) {
     }
     // Nine tiles with two tiles' loads in flight fill the registers (ten tiles, or loads of one or three,
     // spill). 17 to 32 inputs are two workgroups of 16 for each share of the rows, the second reading
-    // them from L2: with all of them in one workgroup the fp64 sums spill at two tiles already
-    // (32 inputs at the OPT-6.7B, 66B, 175B predictors, the whole call: 56, 117, 142 us; this way 37, 68, 87).
+    // them from L2: with all of them in one workgroup the registers hold two tiles and superblocks of one
+    // block (32 inputs at the OPT-6.7B, 66B, 175B predictors, the whole call: 56, 117, 142 us; this way 37, 68, 87).
     a.S = 1;
     const int parts = (a.B + 15) / 16;
     a.G0 = G / parts;
     return launch_rows_v<16, MODE, EPI, XF32, KT, 9, 2, 2>(a, a.G0 * parts, st);
   } else {
     // few rows (to one tile per workgroup): one tile, longer superblocks. Otherwise two tiles'
-    // loads in flight with 16 tokens (four: QKV of the OPT-6.7B heads 29.5 against 24.4 us), one
+    // loads in flight with 16 tokens (four spill: QKV of the OPT-6.7B heads 29.5 against 24.4 us), one
     // with 32 (two spill)
     if constexpr (MODE == kRowsIdentity)
       if (a.src[1].W0 == nullptr && a.src[0].nrows <= 16 * G)

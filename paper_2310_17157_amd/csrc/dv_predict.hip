@@ -461,7 +461,7 @@ static dv_status predict_impl(const dv_predictor* p, const float* x, int32_t B, 
   };
   if (B > 1 && p->wtype == DV_F16) {
     // a batch on fp16 factors: the weights are read once per 32 inputs, on the matrix cores
-    // (16 inputs at the OPT-66B predictor: 12 + 21 us against 62 + 190 us with the weights read
+    // (16 inputs at the OPT-66B predictor: 12 + 22 us against 62 + 190 us with the weights read
     // once per input), but for layers so small that their rows on the matrix cores are a few long chains.
     // Hidden layer, us once per input / on the matrix cores: 2 inputs, rank 1000, width 9216
     // 9.9 / 10.7, 3 inputs 14.1 / 10.9; rank 64: 8 inputs 8.0 / 10.0, 16 inputs 12.9 / 11.0. Scores of
